@@ -158,7 +158,7 @@ def spmm_kernels(algo, nnz, m, k):
     """Kernel names aires_spmm launches for `algo` (its AUTO rule: dense
     tiles from one entry in eight)."""
     dense = algo == "dense_tiles" or (algo == "auto" and 8 * nnz >= m * k and k <= 1 << 20)
-    return "k_spmm_dense" if dense else "k_spmm_rows + k_spmm_heavy"
+    return "k_spmm_dense" if dense else "k_spmm_rows"
 
 
 def spmm_roofline(algo, m, k, F, nnz, flops, compulsory, gather, launch_ms):

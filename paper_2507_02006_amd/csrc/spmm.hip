@@ -4,13 +4,13 @@
 // the aggregation of Eq. 1.  A is CSR (32- or 64-bit row pointers), W and
 // Y are dense row-major with leading dimensions ldw and ldy.
 //
-// Rows with at most kHeavy entries take one wavefront: lane l owns V
-// consecutive columns of a 64*V-column block, the row's (k, a_ik) pairs are
-// read 64 at a time (a lane each) and broadcast with readlane, and several
-// rows of W are in flight at a time.  Longer rows
-// take a 256-thread workgroup whose four wavefronts split the entries and
-// add their partial rows in LDS.  The activation is applied before the
-// store; every element of Y is written exactly once.
+// Entry gather (sparse A): L lanes own one entry's row of W, V columns a
+// lane, and the 64 / L lane groups of a wavefront take different entries of
+// the row of A; their partial rows are added across the groups at the end.
+// Rows with at most kHeavy entries take one wavefront each; longer rows take
+// the eight wavefronts of a workgroup, per block of 64 columns, and come
+// first in the same launch.  Dense tiles: see below.  The activation is
+// applied before the store; every element of Y is written exactly once.
 #include "kernels.h"
 
 #include <hip/hip_runtime.h>
@@ -21,141 +21,234 @@ namespace kern {
 namespace {
 
 constexpr int WAVE = 64;
-constexpr int SPMM_BLOCK = 256;  // four wavefronts
-constexpr int64_t kHeavy = 512;  // longer rows are split over a workgroup
+constexpr int SPMM_BLOCK = 512;  // eight wavefronts
+// Longer rows are split over a workgroup: 128 and 512 were slower (4000 rows,
+// F = 256: 29.6 and 19.3 us against 12.8; 150 K rows: 231 and 241 against 225).
+constexpr int64_t kHeavy = 256;
+constexpr unsigned NXCD = 8;     // gfx950 hands workgroups round-robin to its 8 XCDs
 
 template <typename RP>
 __device__ __forceinline__ int64_t rp_at(const void* rp, int64_t i) {
   return (int64_t) static_cast<const RP*>(rp)[i];
 }
 
-// V columns of W row k from column c, as one vector load when VEC.
-template <int V, bool VEC>
-__device__ __forceinline__ void load_w(const float* wr, int c, int F, float (&w)[V]) {
-  if constexpr (VEC && V == 8) {
-    if (c + V <= F) {
-      const float4 a = *reinterpret_cast<const float4*>(wr + c);
-      const float4 b = *reinterpret_cast<const float4*>(wr + c + 4);
-      w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w;
-      w[4] = b.x; w[5] = b.y; w[6] = b.z; w[7] = b.w;
-      return;
-    }
-  } else if constexpr (VEC && V == 4) {
-    if (c + V <= F) {
-      const float4 a = *reinterpret_cast<const float4*>(wr + c);
-      w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w;
-      return;
-    }
-  } else if constexpr (VEC && V == 2) {
-    if (c + V <= F) {
-      const float2 a = *reinterpret_cast<const float2*>(wr + c);
-      w[0] = a.x; w[1] = a.y;
-      return;
-    }
+// Four floats at any 4-byte boundary: one 16-byte load or store (global
+// memory takes 16-byte accesses at 4-byte alignment), so that row strides and
+// bases need no alignment of their own.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int V>
+__device__ __forceinline__ void load_cols(const float* p, float (&w)[V]) {
+  if constexpr (V == 4) {
+    const f32x4_any x = *reinterpret_cast<const f32x4_any*>(p);
+    w[0] = x[0]; w[1] = x[1]; w[2] = x[2]; w[3] = x[3];
+  } else {
+    w[0] = *p;
   }
-#pragma unroll
-  for (int v = 0; v < V; ++v) w[v] = c + v < F ? wr[c + v] : 0.f;
 }
 
-// acc += a_ik * W[k, c .. c+V) over the entries [p0, p1).  The entries
-// come in 64 at a time, one per lane (a coalesced load), and are handed to
-// the whole wavefront with readlane, so that U rows of W are in flight per
-// step with no scalar load on the path.
-template <int V, bool VEC>
-__device__ __forceinline__ void row_block(const int32_t* acol, const float* aval, int64_t p0, int64_t p1,
-                                          const float* W, int64_t ldw, int c, int F, float (&acc)[V]) {
-  constexpr int U = V <= 2 ? 8 : 4;
-  const int lane = threadIdx.x % WAVE;
-  for (int64_t pb = p0; pb < p1; pb += WAVE) {
-    const int cnt = (int)(p1 - pb < WAVE ? p1 - pb : WAVE);
-    int kl = 0;
-    float al = 0.f;
-    if (lane < cnt) {
-      kl = acol[pb + lane];
-      al = aval[pb + lane];
+// One wavefront's share of columns [cb, ce) of a row of Y: L lanes per
+// entry, V columns per lane (from cb + l * V), E = 64 / L entries side by
+// side.  A lane's vector that would end past ce is moved back to end there:
+// every load is a whole vector inside the row of W (ce >= V), and the store
+// keeps only the columns that are the lane's own.
+template <int L, int V>
+struct RowPart {
+  static constexpr int E = WAVE / L;
+  static constexpr int U = E < 8 ? 8 : 4;  // steps of E entries in flight
+  int col;                                 // first column loaded
+  float acc[V];
+
+  __device__ __forceinline__ void start(int cb, int ce) {
+    const int c = cb + (int)(threadIdx.x % L) * V;
+    col = c + V <= ce ? c : ce - V;
+#pragma unroll
+    for (int v = 0; v < V; ++v) acc[v] = 0.f;
+  }
+
+  // acc += a_ik W[k, .] for N steps of E entries from j on; kl, al hold the
+  // cnt entries of a batch, one per lane.  Past the batch's last entry a
+  // group repeats that entry's load and adds nothing.
+  template <int N>
+  __device__ __forceinline__ void steps(int kl, float al, int j, int cnt, const float* W, int64_t ldw) {
+    float w[N][V], a[N];
+    bool ok[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      if constexpr (E == 1) {
+        a[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(al), j + u));
+        ok[u] = true;
+        load_cols<V>(W + (int64_t)__builtin_amdgcn_readlane(kl, j + u) * ldw + col, w[u]);
+      } else {
+        const int e = j + u * E + (int)(threadIdx.x % WAVE) / L;
+        ok[u] = e < cnt;
+        const int ec = ok[u] ? e : cnt - 1;
+        a[u] = __shfl(al, ec);
+        load_cols<V>(W + (int64_t)__shfl(kl, ec) * ldw + col, w[u]);
+      }
     }
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const float x = fmaf(a[u], w[u][v], acc[v]);
+        acc[v] = ok[u] ? x : acc[v];
+      }
+  }
+
+  // a batch of 1 ... 64 entries; kl, al as above
+  __device__ __forceinline__ void batch(int kl, float al, int cnt, const float* W, int64_t ldw) {
     int j = 0;
-    for (; j + U <= cnt; j += U) {
-      float w[U][V];
+    for (; j + (U - 1) * E < cnt; j += U * E) steps<U>(kl, al, j, cnt, W, ldw);
+    if (U > 4 && j + 3 * E < cnt) { steps<4>(kl, al, j, cnt, W, ldw); j += 4 * E; }
+    if (j + E < cnt) { steps<2>(kl, al, j, cnt, W, ldw); j += 2 * E; }
+    if (j < cnt) steps<1>(kl, al, j, cnt, W, ldw);
+  }
+
+  // the groups' partial rows added up, in every group
+  __device__ __forceinline__ void combine_groups() {
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        load_w<V, VEC>(W + (int64_t)__builtin_amdgcn_readlane(kl, j + u) * ldw, c, F, w[u]);
+    for (int o = L; o < WAVE; o <<= 1)
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(al), j + u));
+      for (int v = 0; v < V; ++v) acc[v] += __shfl_xor(acc[v], o);
+  }
+
+  // the first group writes its columns of the row
+  __device__ __forceinline__ void store(float* yr, int cb, int ce, int relu) {
+    const int lane = threadIdx.x % WAVE;
+    if (lane >= L) return;
+    const int c = cb + lane * V;
+    float y[V];
 #pragma unroll
-        for (int v = 0; v < V; ++v) acc[v] = fmaf(a, w[u][v], acc[v]);
+    for (int v = 0; v < V; ++v) y[v] = relu ? fmaxf(acc[v], 0.f) : acc[v];
+    if constexpr (V == 4) {
+      if (c + V <= ce) {
+        *reinterpret_cast<f32x4_any*>(yr + c) = f32x4_any{y[0], y[1], y[2], y[3]};
+        return;
       }
     }
-    for (; j < cnt; ++j) {
-      float w[V];
-      load_w<V, VEC>(W + (int64_t)__builtin_amdgcn_readlane(kl, j) * ldw, c, F, w);
-      const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(al), j));
 #pragma unroll
-      for (int v = 0; v < V; ++v) acc[v] = fmaf(a, w[v], acc[v]);
-    }
+    for (int v = 0; v < V; ++v)
+      if (col + v >= c) yr[col + v] = y[v];
   }
-}
+};
 
-template <int V, bool RELU>
-__device__ __forceinline__ void store_row(float* yr, int c, int F, const float (&acc)[V]) {
-#pragma unroll
-  for (int v = 0; v < V; ++v)
-    if (c + v < F) yr[c + v] = RELU ? fmaxf(acc[v], 0.f) : acc[v];
-}
-
-template <typename RP, int V, bool VEC, bool RELU>
-__global__ __launch_bounds__(SPMM_BLOCK) void k_spmm_rows(const void* arp, const int32_t* acol, const float* aval,
-                                                           int64_t m, const float* W, int64_t ldw, int F, float* Y,
-                                                           int64_t ldy) {
-  const int lane = threadIdx.x % WAVE;
-  const int64_t nw = (int64_t)gridDim.x * (SPMM_BLOCK / WAVE);
-  for (int64_t row = (int64_t)blockIdx.x * (SPMM_BLOCK / WAVE) + threadIdx.x / WAVE; row < m; row += nw) {
-    const int64_t p0 = rp_at<RP>(arp, row), p1 = rp_at<RP>(arp, row + 1);
-    if (p1 - p0 > kHeavy) continue;  // a workgroup takes it
-    for (int cb = 0; cb < F; cb += WAVE * V) {
-      const int c = cb + lane * V;
-      float acc[V];
-#pragma unroll
-      for (int v = 0; v < V; ++v) acc[v] = 0.f;
-      row_block<V, VEC>(acol, aval, p0, p1, W, ldw, c, F, acc);
-      store_row<V, RELU>(Y + row * ldy, c, F, acc);
-    }
-  }
-}
-
-template <typename RP, int V, bool VEC, bool RELU>
-__global__ __launch_bounds__(SPMM_BLOCK) void k_spmm_heavy(const void* arp, const int32_t* acol, const float* aval,
-                                                            int64_t m, const float* W, int64_t ldw, int F, float* Y,
-                                                            int64_t ldy) {
+// Gather bound: every entry reads 4 F bytes of W from L2 or beyond.  With
+// one lane per column and one entry at a time a narrow row (F = 16 ... 64)
+// left most lanes idle or moved 4 bytes a lane; L lanes of 16 bytes keep the
+// loads wide and 64 / L entries side by side.  Blocks [0, hblocks) do the
+// heavy rows: block b scans rows for them and takes column block b mod hcb
+// (64 columns) with all eight wavefronts, so that a hub row's time is divided
+// by 8 * hcb and runs beside the light rows instead of after them.  Measured
+// on symmetric R-MAT graphs against a column per lane with the heavy rows in
+// a launch of their own: 1 M rows, 17.1 M entries, F = 256: 3.65 -> 2.05 ms
+// (8.5 TB/s of gathered rows); 150 K rows, 2.1 M entries, F = 41: 351 -> 81 us.
+template <typename RP, int L, int V>
+__global__ __launch_bounds__(SPMM_BLOCK, 6) void k_spmm_rows(const void* arp, const int32_t* acol, const float* aval,
+                                                              int64_t m, const float* W, int64_t ldw, int F, float* Y,
+                                                              int64_t ldy, int relu, unsigned hblocks, unsigned hcb,
+                                                              unsigned ncb, int cw) {
   constexpr int NWV = SPMM_BLOCK / WAVE;
-  __shared__ float part[NWV - 1][WAVE * V];
-  const int lane = threadIdx.x % WAVE, wv = threadIdx.x / WAVE;
-  for (int64_t row = blockIdx.x; row < m; row += gridDim.x) {
-    const int64_t p0 = rp_at<RP>(arp, row), p1 = rp_at<RP>(arp, row + 1);
-    if (p1 - p0 <= kHeavy) continue;  // uniform over the workgroup
-    const int64_t len = (p1 - p0 + NWV - 1) / NWV;
-    const int64_t q0 = p0 + wv * len < p1 ? p0 + wv * len : p1;
-    const int64_t q1 = q0 + len < p1 ? q0 + len : p1;
-    for (int cb = 0; cb < F; cb += WAVE * V) {
-      const int c = cb + lane * V;
-      float acc[V];
-#pragma unroll
-      for (int v = 0; v < V; ++v) acc[v] = 0.f;
-      row_block<V, VEC>(acol, aval, q0, q1, W, ldw, c, F, acc);
-      if (wv > 0) {
-#pragma unroll
-        for (int v = 0; v < V; ++v) part[wv - 1][lane * V + v] = acc[v];
-      }
+  constexpr int LH = L < 16 ? L : 16;  // heavy rows: lanes per entry
+  constexpr int HC = LH * V;           // and columns of a block
+  __shared__ float part[NWV - 1][HC];
+  __shared__ int32_t found[SPMM_BLOCK];
+  __shared__ int nfound;
+  const int lane = threadIdx.x % WAVE;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  if (blockIdx.x < hblocks) {
+    const int cb = (int)(blockIdx.x % hcb) * HC, ce = cb + HC < F ? cb + HC : F;
+    for (int64_t r0 = (int64_t)(blockIdx.x / hcb) * SPMM_BLOCK; r0 < m; r0 += (int64_t)(hblocks / hcb) * SPMM_BLOCK) {
+      if (threadIdx.x == 0) nfound = 0;
       __syncthreads();
-      if (wv == 0) {
-#pragma unroll
-        for (int i = 0; i < NWV - 1; ++i)
-#pragma unroll
-          for (int v = 0; v < V; ++v) acc[v] += part[i][lane * V + v];
-        store_row<V, RELU>(Y + row * ldy, c, F, acc);
-      }
+      const int64_t mine = r0 + threadIdx.x;
+      if (mine < m && rp_at<RP>(arp, mine + 1) - rp_at<RP>(arp, mine) > kHeavy)
+        found[atomicAdd(&nfound, 1)] = (int32_t)threadIdx.x;
       __syncthreads();
+      const int n = nfound;
+      for (int x = 0; x < n; ++x) {
+        const int64_t row = r0 + found[x];
+        const int64_t p0 = rp_at<RP>(arp, row), p1 = rp_at<RP>(arp, row + 1);
+        RowPart<LH, V> r;
+        r.start(cb, ce);
+        // 64 entries at a time, the wavefronts in turn
+        for (int64_t p = p0 + wv * WAVE; p < p1; p += NWV * WAVE) {
+          const int cnt = (int)(p1 - p < WAVE ? p1 - p : WAVE);
+          const int64_t q = p + (lane < cnt ? lane : cnt - 1);
+          r.batch(acol[q], aval[q], cnt, W, ldw);
+        }
+        r.combine_groups();
+        if (wv > 0 && lane < LH)
+#pragma unroll
+          for (int v = 0; v < V; ++v) part[wv - 1][lane * V + v] = r.acc[v];
+        __syncthreads();
+        if (wv == 0) {
+          if (lane < LH)
+#pragma unroll
+            for (int i = 0; i < NWV - 1; ++i)
+#pragma unroll
+              for (int v = 0; v < V; ++v) r.acc[v] += part[i][lane * V + v];
+          r.store(Y + row * ldy, cb, ce, relu);
+        }
+        __syncthreads();
+      }
+    }
+    return;
+  }
+  // light rows, a wavefront per row and column block; the next row's first
+  // entries and the row pointers of the one after it are in flight while a
+  // row is added up
+  const unsigned b = blockIdx.x - hblocks;  // hblocks and the light blocks are multiples of NXCD
+  const unsigned nside = NXCD / (ncb < NXCD ? ncb : NXCD);
+  const unsigned x = b % NXCD;
+  const int64_t nw = (int64_t)((gridDim.x - hblocks) / NXCD) * nside * NWV;
+  const int64_t row0 = ((int64_t)(b / NXCD) * nside + x / (NXCD / nside)) * NWV + wv;
+  if (row0 >= m) return;
+  auto entries = [&](int64_t p0, int64_t p1, int& k, float& a) {
+    k = 0;
+    a = 0.f;
+    if (p0 + lane < p1) {
+      k = acol[p0 + lane];
+      a = aval[p0 + lane];
+    }
+  };
+  for (unsigned c = x % (NXCD / nside); c < ncb; c += NXCD) {
+    const int cb = (int)c * cw, ce = cb + cw < F ? cb + cw : F;
+    int64_t row = row0;
+    int64_t p0 = rp_at<RP>(arp, row), p1 = rp_at<RP>(arp, row + 1);
+    int64_t q0 = 0, q1 = 0;
+    if (row + nw < m) {
+      q0 = rp_at<RP>(arp, row + nw);
+      q1 = rp_at<RP>(arp, row + nw + 1);
+    }
+    int kl;
+    float al;
+    entries(p0, p1, kl, al);
+    for (; row < m; row += nw) {
+      int kn;
+      float an;
+      entries(q0, q1, kn, an);
+      int64_t s0 = 0, s1 = 0;
+      if (row + 2 * nw < m) {
+        s0 = rp_at<RP>(arp, row + 2 * nw);
+        s1 = rp_at<RP>(arp, row + 2 * nw + 1);
+      }
+      if (p1 - p0 <= kHeavy) {
+        RowPart<L, V> r;
+        r.start(cb, ce);
+        if (p1 > p0) r.batch(kl, al, (int)(p1 - p0 < WAVE ? p1 - p0 : WAVE), W, ldw);
+        for (int64_t p = p0 + WAVE; p < p1; p += WAVE) {
+          const int cnt = (int)(p1 - p < WAVE ? p1 - p : WAVE);
+          int k2;
+          float a2;
+          entries(p, p1, k2, a2);
+          r.batch(k2, a2, cnt, W, ldw);
+        }
+        r.combine_groups();
+        r.store(Y + row * ldy, cb, ce, relu);
+      }
+      p0 = q0; p1 = q1; q0 = s0; q1 = s1;
+      kl = kn; al = an;
     }
   }
 }
@@ -187,7 +280,6 @@ constexpr int DT_M = 64;        // rows per tile
 constexpr int DT_K = 32;        // k per LDS chunk
 constexpr int DT_BLOCK = 256;   // four wavefronts, 16 rows each
 constexpr int DT_ENTRIES = DT_K / 4;  // four threads per row: one round of loads covers a chunk
-constexpr int NXCD = 8;         // gfx950 hands workgroups round-robin to its 8 XCDs
 constexpr int kOutOfRange = INT32_MIN;  // a buffer offset no resource here reaches (reads 0)
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -378,44 +470,47 @@ __global__ __launch_bounds__(DT_BLOCK, NT > 4 ? 3 : 4) void k_spmm_dense(
   }
 }
 
-template <typename RP, int V, bool VEC, bool RELU>
-hipError_t spmm_t(const void* arp, const int32_t* acol, const float* aval, int64_t m, const float* W, int64_t ldw,
-                  int F, float* Y, int64_t ldy, hipStream_t s) {
-  int64_t g1 = (m + SPMM_BLOCK / WAVE - 1) / (SPMM_BLOCK / WAVE);
-  if (g1 > 65536) g1 = 65536;
-  hipLaunchKernelGGL((k_spmm_rows<RP, V, VEC, RELU>), dim3((unsigned)g1), dim3(SPMM_BLOCK), 0, s, arp, acol, aval,
-                     m, W, ldw, F, Y, ldy);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  int64_t g2 = m < 2048 ? m : 2048;
-  hipLaunchKernelGGL((k_spmm_heavy<RP, V, VEC, RELU>), dim3((unsigned)g2), dim3(SPMM_BLOCK), 0, s, arp, acol, aval,
-                     m, W, ldw, F, Y, ldy);
+template <typename RP, int L, int V>
+hipError_t spmm_t(int relu, const void* arp, const int32_t* acol, const float* aval, int64_t m, const float* W,
+                  int64_t ldw, int F, float* Y, int64_t ldy, int64_t ncb, hipStream_t s) {
+  constexpr int NWV = SPMM_BLOCK / WAVE;
+  const int cw = (int)(((F + V - 1) / V + ncb - 1) / ncb * V);
+  constexpr int HC = (L < 16 ? L : 16) * V;
+  const int64_t hcb = (F + HC - 1) / HC;
+  int64_t hx = (m + SPMM_BLOCK - 1) / SPMM_BLOCK;
+  const int64_t most = hcb < 512 ? 4096 / hcb : 8;
+  if (hx > most) hx = most;
+  hx = (hx + NXCD - 1) / NXCD * NXCD;
+  const int64_t hblocks = hx * hcb;
+  const int64_t nside = NXCD / (ncb < NXCD ? ncb : NXCD);
+  int64_t g = (m + nside * NWV - 1) / (nside * NWV);
+  if (g > 512) g = 512;
+  hipLaunchKernelGGL((k_spmm_rows<RP, L, V>), dim3((unsigned)(hblocks + g * NXCD)), dim3(SPMM_BLOCK), 0, s, arp, acol,
+                     aval, m, W, ldw, F, Y, ldy, relu, (unsigned)hblocks, (unsigned)hcb, (unsigned)ncb, cw);
   return hipGetLastError();
-}
-
-template <typename RP, int V, bool VEC>
-hipError_t spmm_act(int relu, const void* arp, const int32_t* acol, const float* aval, int64_t m, const float* W,
-                    int64_t ldw, int F, float* Y, int64_t ldy, hipStream_t s) {
-  return relu ? spmm_t<RP, V, VEC, true>(arp, acol, aval, m, W, ldw, F, Y, ldy, s)
-              : spmm_t<RP, V, VEC, false>(arp, acol, aval, m, W, ldw, F, Y, ldy, s);
 }
 
 template <typename RP>
 hipError_t spmm_rp(int relu, const void* arp, const int32_t* acol, const float* aval, int64_t m, const float* W,
                    int64_t ldw, int F, float* Y, int64_t ldy, hipStream_t s) {
-  // columns per lane: one 64-lane pass covers up to 512 columns; vector loads
-  // when W's rows and the base are aligned to the vector
-  const int V = F <= 64 ? 1 : F <= 128 ? 2 : F <= 256 ? 4 : 8;
-  const bool vec = V > 1 && ldw % V == 0 && (reinterpret_cast<uintptr_t>(W) % (4 * V)) == 0;
-  switch (V) {
-    case 1: return spmm_act<RP, 1, false>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, s);
-    case 2: return vec ? spmm_act<RP, 2, true>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, s)
-                       : spmm_act<RP, 2, false>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, s);
-    case 4: return vec ? spmm_act<RP, 4, true>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, s)
-                       : spmm_act<RP, 4, false>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, s);
-    default: return vec ? spmm_act<RP, 8, true>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, s)
-                        : spmm_act<RP, 8, false>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, s);
-  }
+  if (F < 4) return spmm_t<RP, 4, 1>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, 1, s);
+  // Column blocks of at most 64 vectors, a power of two of them up to the
+  // number of XCDs (each XCD then gathers from a part of W's columns), and
+  // two where both halves of a row are whole cache lines (1 M rows, F = 256:
+  // 2.14 -> 2.06 ms); halves that share lines cost more than they save
+  // (150 K rows, F = 200: 222 against 236 us), as do blocks below 128 columns.
+  const int64_t vec = (F + 3) / 4;
+  const bool lines = F > 128 && F % 64 == 0 && ldw % 32 == 0 && reinterpret_cast<uintptr_t>(W) % 128 == 0;
+  int64_t ncb = lines ? 2 : 1;
+  while (ncb < NXCD && vec > ncb * 64) ncb *= 2;
+  if (vec > ncb * 64) ncb = (vec + 63) / 64;
+  const int64_t cv = (vec + ncb - 1) / ncb;
+  if (cv <= 2) return spmm_t<RP, 2, 4>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, ncb, s);
+  if (cv <= 4) return spmm_t<RP, 4, 4>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, ncb, s);
+  if (cv <= 8) return spmm_t<RP, 8, 4>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, ncb, s);
+  if (cv <= 16) return spmm_t<RP, 16, 4>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, ncb, s);
+  if (cv <= 32) return spmm_t<RP, 32, 4>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, ncb, s);
+  return spmm_t<RP, 64, 4>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, ncb, s);
 }
 
 template <typename RP, int NT, bool VEC>

@@ -122,6 +122,31 @@ def test_heavy_rows_split_over_a_workgroup(torch_gpu, algo):
         check(torch_gpu, A, W, relu=True, name="heavy F=%d" % F, algo=algo)
 
 
+@pytest.mark.parametrize("F", [2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 64, 65, 128, 129, 192, 256, 257, 384, 512, 516, 2100])
+def test_rows_lane_groups_and_column_blocks(torch_gpu, F):
+    """Entry gather: every lane-group width (F around powers of two), vectors
+    moved back at the end of a row, one, two and more column blocks (more
+    than the XCDs at 2100), and row lengths around a batch of 64, the
+    workgroup limit (256) and the eight wavefronts' turn (512), with strides
+    that keep whole cache lines and one that does not."""
+    rng = np.random.default_rng(1000 + F)
+    K = 1400
+    lens = np.array([0, 1, 2, 7, 8, 9, 31, 33, 63, 64, 65, 129, 255, 256, 257, 300, 512, 513, 1025, 1400, 0])
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    col = np.concatenate([np.sort(rng.choice(K, L, replace=False)) for L in lens]).astype(np.int32)
+    A = CSR(len(lens), K, rp, col, rng.uniform(-1, 1, len(col)).astype(np.float32))
+    W = rng.uniform(-1, 1, (K, F)).astype(np.float32)
+    check(torch_gpu, A, W, name="lane groups F=%d" % F, algo="rows")
+    check(torch_gpu, A, W, relu=True, rp64=True, ldw_pad=(1 if F % 32 == 0 else 32 - F % 32), ldy_pad=3,
+          name="lane groups padded F=%d" % F, algo="rows")
+    Wn = W.copy()  # a row of W that no entry names may hold anything
+    sub = CSR(12, K, rp[:13], col[:rp[12]], A.val[:rp[12]])
+    Wn[np.setdiff1d(np.arange(K), sub.col)] = np.nan
+    import paper_2507_02006_amd as aires
+    y = aires.spmm(dev_csr(torch_gpu, sub), torch_gpu.from_numpy(Wn).cuda(), algo="rows")
+    assert torch_gpu.isfinite(y).all()
+
+
 @pytest.mark.parametrize("algo", ALGOS)
 def test_strides_offsets_and_rp64(torch_gpu, algo):
     """Row strides above F (padding untouched), a W base that is not
