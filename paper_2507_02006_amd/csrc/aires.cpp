@@ -332,11 +332,27 @@ struct aires_plan {
 
 namespace {
 
+// Presence bitmaps of B's rows pay where a row's bitmap (narrow_words(N)
+// words) is at most four times the bytes of its columns on average.
+bool narrow_bitmaps_pay(const aires_csr& B) {
+  return B.ncols >= 1 && B.ncols <= kern::NARROW_MAX_COLS && B.nrows > 0 && B.nnz > 0 &&
+         kern::narrow_words(B.ncols) * B.nrows <= 4 * B.nnz;
+}
+
 void bin_plan(aires_plan* p) {
   const int64_t N = p->B.ncols;
   const aires_plan_opts& o = p->opts;
   const int64_t dense_max = o.dense_max_cols > 0 ? std::min<int64_t>(o.dense_max_cols, kDenseMaxCols) : kDenseMaxCols;
-  const int64_t wave_max = o.wave_max_products > 0 ? o.wave_max_products : kWaveMaxProducts;
+  int64_t wave_max = o.wave_max_products > 0 ? o.wave_max_products : kWaveMaxProducts;
+  if (o.wave_max_products <= 0 && narrow_bitmaps_pay(p->B)) {
+    // a wavefront's longest row at about a quarter of the mean work of the
+    // chip's 8192 wavefront slots, so that it does not outlast the launch
+    // (numeric phase, 4096 rows and 1.5 M products: 92 us at 8192, 68 at
+    // 1024; 8.4 M rows and 2.6 G products: 8.4 ms at 1024, 6.5 at 16384)
+    const int64_t tiles = p->A.mem == AIRES_MEM_DEVICE ? 1 : kStreamTiles;
+    const double products = (double)p->A.nnz * ((double)p->B.nnz / (double)p->B.nrows) / (double)tiles;
+    wave_max = (int64_t)std::min(16384.0, std::max(1024.0, products / 32768.0));
+  }
   const int64_t split_min = o.split_min_products > 0   ? o.split_min_products
                             : o.split_min_products < 0 ? 0  // < 0: no split rows
                                                        : kSplitMinProducts;
@@ -1381,7 +1397,61 @@ struct TileWs {
   int64_t bm_cap = 0;
   unsigned long long* bm_top = nullptr;
   bool item_cut = false;          // the call started with a bitmap cache (window cuts of kept rows)
+  kern::NarrowView narrow;        // bitmaps and slots of a narrow product (words 0: none)
+  int64_t products = 0;           // host copy, after the symbolic phase
 };
+
+// Whether this plan's B rows may be read as presence bitmaps.
+bool narrow_pays(const aires_plan* p) {
+  return p->th.nb > 1 && p->th.kind[1] == kern::KIND_DENSE_WAVE && narrow_bitmaps_pay(p->B);
+}
+
+// The bitmaps of B's rows (K) and of C's rows (rows in all), the slots of B's
+// rows and the part list of a tile of up to nnz entries are optional
+// workspace: taken where the budget left free by the plan (or half of what
+// is left of a fixed arena) holds them, so that no call needs more than it
+// was planned with.  One block holds them all.  copies: how many of the C
+// bitmaps and part lists are needed (two slots of a streamed A).
+aires_status alloc_narrow(aires_plan* p, DevPool& ws, int64_t rows, int64_t nnz, int copies, kern::NarrowView* nv) {
+  for (int i = 0; i < copies; ++i) nv[i] = kern::NarrowView{};
+  // (C's arrays under Eq. 5 are an estimate that may have to grow)
+  if (!narrow_pays(p) || (copies > 1 && p->opts.c_bound == AIRES_CBOUND_PAPER_EQ5)) return AIRES_OK;
+  const int64_t K = p->B.nrows, words = kern::narrow_words(p->B.ncols);
+  const int64_t nparts = nnz / kern::NARROW_LONG + 1;
+  // (of a fixed arena, half of what is left beyond the slots of a few split rows)
+  const int64_t room = ws.arena ? (ws.left() - (int64_t(64) << 10)) / 2 : p->budget - p->info.peak_bytes;
+  kern::NarrowView v;
+  bool slots = kern::narrow_slots(p->B.ncols, K, p->B.nnz, &v);
+  auto r256 = DevPool::round256;
+  const int64_t sz_bbm = r256(4 * words * K), sz_cbm = r256(4 * words * std::max<int64_t>(rows, 1));
+  const int64_t sz_parts = r256((int64_t)sizeof(kern::NarrowPart) * nparts + 4);
+  int64_t need = 0;
+  auto fits = [&] {
+    need = sz_bbm + (slots ? r256(K * v.slot) : 0) + copies * (sz_cbm + sz_parts);
+    return need <= room && ws.fits(need);
+  };
+  if (!fits() && slots) slots = false;
+  if (!fits()) return AIRES_OK;
+  void* block = nullptr;
+  ST_TRY(ws.get((size_t)need, &block));
+  char* at = static_cast<char*>(block);
+  auto carve = [&](int64_t bytes) {
+    char* x = at;
+    at += bytes;
+    return x;
+  };
+  v.words = (int32_t)words;
+  v.bbm = reinterpret_cast<uint32_t*>(carve(sz_bbm));
+  if (slots) v.slots = reinterpret_cast<unsigned char*>(carve(r256(K * v.slot)));
+  else v.slot = v.cap = v.lanes = 0;
+  for (int i = 0; i < copies; ++i) {
+    nv[i] = v;
+    nv[i].cbm = reinterpret_cast<uint32_t*>(carve(sz_cbm));
+    nv[i].parts = reinterpret_cast<kern::NarrowPart*>(carve(sz_parts));
+    nv[i].nparts = reinterpret_cast<int32_t*>(nv[i].parts + nparts);
+  }
+  return AIRES_OK;
+}
 
 // with_list_gcnt: the per-row arrays (products, bin list, grain and window
 // counts) for n rows; without, the caller points them into arrays of its own
@@ -1444,14 +1514,29 @@ kern::WindowParams window_params(const aires_plan* p, const TileWs& w) {
 // analyze + bin + symbolic + scan of one tile; counts land in crp[1..n] and
 // are scanned in place on top of crp[0].  Wide rows also get their window
 // counts scanned into w.icount.
-aires_status tile_symbolic(aires_plan* p, const kern::Operands& op, int64_t n, TileWs& w, int64_t* crp,
+aires_status tile_symbolic(aires_plan* p, const kern::Operands& op, int64_t n, int64_t nnz, TileWs& w, int64_t* crp,
                            unsigned long long* prod_total, hipStream_t s, Timer& tm) {
   const int e0 = tm.record();
   tm.at(aires_plan::T_C0, e0);
   HIP_TRY(hipMemsetAsync(w.cntcur, 0, sizeof(int32_t) * (2 * kern::MAX_BINS + 1), s));
+  if (w.narrow.words) {
+    // products, patterns and counts of C's rows in one pass
+    HIP_TRY(hipMemsetAsync(w.narrow.nparts, 0, sizeof(int32_t), s));
+    HIP_TRY(kern::narrow_symbolic(op, n, nnz, w.narrow, w.P, crp + 1, prod_total, s));
+    const int e1 = tm.record();
+    HIP_TRY(kern::bin_rows(w.P, n, p->th, w.cntcur, w.binoff, w.list, &w.narrow, crp + 1, s));
+    const int e2 = tm.record();
+    HIP_TRY(kern::scan_inplace(crp + 1, n, w.scan_ws, s));
+    const int e3 = tm.record();
+    tm.mark(kern::KIND_DENSE_WAVE, 0, e0, e1);
+    tm.mark(PH_SYMBOLIC, 0, e0, e1);
+    tm.mark(PH_BIN, 0, e1, e2);
+    tm.mark(PH_SCAN, 0, e2, e3);
+    return AIRES_OK;
+  }
   HIP_TRY(kern::analyze(op, n, w.P, prod_total, w.cntcur + 2 * kern::MAX_BINS, w.list, s));
   const int e1 = tm.record();
-  HIP_TRY(kern::bin_rows(w.P, n, p->th, w.cntcur, w.binoff, w.list, s));
+  HIP_TRY(kern::bin_rows(w.P, n, p->th, w.cntcur, w.binoff, w.list, nullptr, nullptr, s));
   HIP_TRY(hipMemsetAsync(crp + 1, 0, sizeof(int64_t) * (size_t)std::max<int64_t>(n, 0), s));
   if (p->wide) HIP_TRY(hipMemsetAsync(w.icount, 0, sizeof(int64_t) * (size_t)(n + 1), s));
   const int e2 = tm.record();
@@ -1485,19 +1570,25 @@ aires_status tile_symbolic(aires_plan* p, const kern::Operands& op, int64_t n, T
   return AIRES_OK;
 }
 
-aires_status tile_numeric(aires_plan* p, const kern::Operands& op, int64_t n, const TileWs& w, const int64_t* crp,
-                          int32_t* ccol, float* cval, int64_t c_base, hipStream_t s, Timer& tm) {
+aires_status tile_numeric(aires_plan* p, const kern::Operands& op, int64_t n, int64_t nnz, const TileWs& w,
+                          const int64_t* crp, int32_t* ccol, float* cval, int64_t c_base, hipStream_t s, Timer& tm) {
   kern::Outputs out{};
   out.crp = crp;
   out.ccol = ccol - c_base;
   out.cval = cval - c_base;
+  // slots pay while the B rows that the products touch mostly fit them
+  const bool slots = w.narrow.words && w.narrow.slots && w.products <= nnz * w.narrow.cap;
   const int e0 = tm.record();
   for (int b = 0; b < p->th.nb; ++b) {
     const int kind = p->th.kind[b];
     if (kind == kern::KIND_EMPTY) continue;
     kern::BinView bv{w.list, w.binoff, b};
     const int ka = tm.record();
-    if (kind == kern::KIND_WINDOWS) {
+    if (slots && kind == kern::KIND_DENSE_WAVE) {
+      HIP_TRY(kern::narrow_rows(op, w.narrow, w.P, n, p->th.max_p[b], out, s));
+    } else if (slots && (kind == kern::KIND_DENSE_BLOCK || kind == kern::KIND_DENSE_SPLIT)) {
+      HIP_TRY(kern::narrow_block(op, w.narrow, bv, kind == kern::KIND_DENSE_SPLIT ? &w.split : nullptr, n, out, s));
+    } else if (kind == kern::KIND_WINDOWS) {
       while (bv.last() + 1 < p->th.nb && p->th.kind[bv.last() + 1] == kern::KIND_WINDOWS) bv.bin_last = bv.last() + 1;
       HIP_TRY(kern::windows_numeric(op, bv, window_params(p, w), out, n, w.nitems, s));
       b = bv.last();
@@ -1619,6 +1710,12 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
     }
   }
   const bool item_cut = bm_cache != nullptr;  // kept for the call, even if the cache is released later
+  // narrow products: the bitmaps of C's rows are one array (a tile's part
+  // starts at its first row), the part list is shared by the tiles
+  kern::NarrowView narrow;
+  int64_t max_nnz = 0;
+  for (const auto& t : p->tiles) max_nnz = std::max(max_nnz, t.nnz1 - t.nnz0);
+  ST_TRY(alloc_narrow(p, ws, m, max_nnz, 1, &narrow));
   ST_TRY(alloc_split_ws(p, ws, shared.split));
   auto tile_ws = [&](int64_t t) {
     const aires_tile& T = p->tiles[(size_t)t];
@@ -1627,6 +1724,8 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
     w.item_cut = item_cut;
     w.list = list + T.r0;
     w.binoff = binoff + t * (kern::MAX_BINS + 1);
+    w.narrow = narrow;
+    if (narrow.words) w.narrow.cbm = narrow.cbm + T.r0 * narrow.words;
     if (p->wide) {
       w.gcnt = gcnt + T.r0 * (int64_t)p->nG;
       w.icount = icount + T.r0 + t;
@@ -1648,6 +1747,11 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
                                      p->nG, bidx, index_bmax(p, bidx), s));
     tm.mark(PH_INDEX, 0, ea, tm.record());
   }
+  if (narrow.words) {
+    const int ea = tm.record();
+    HIP_TRY(kern::narrow_prepare(p->B.row_ptr, p->B.rp_type == AIRES_IDX_I64, p->B.col_idx, p->B.vals, K, N, narrow, s));
+    tm.mark(PH_INDEX, 0, ea, tm.record());
+  }
 
   // Sweep 1: symbolic phase of every tile; C.row_ptr grows tile by tile.
   for (int64_t t = 0; t < nt; ++t) {
@@ -1657,7 +1761,7 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
     kern::Operands op = tile_operands(p, arp, 0, p->A.col_idx, avals, p->B.row_ptr, p->B.col_idx,
                                       p->B.vals, bidx);
     tm.tile = (int)t;
-    ST_TRY(tile_symbolic(p, op, T.r1 - T.r0, w, crp + T.r0, prod + t, s, tm));
+    ST_TRY(tile_symbolic(p, op, T.r1 - T.r0, T.nnz1 - T.nnz0, w, crp + T.r0, prod + t, s, tm));
   }
   tm.tile = -1;
   // The one host synchronisation: nnz(C) (and the window count of every
@@ -1699,6 +1803,12 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
     bm_cache = nullptr;
     bm_cap = 0;
   }
+  if (narrow.words && !ws.fits(need)) {
+    // the bitmaps of a narrow product go before C is refused too: the numeric
+    // kernels without them need only the row bins
+    ws.give_back(const_cast<uint32_t*>(narrow.bbm));  // the first part of their block
+    narrow.words = 0;
+  }
   int32_t* ccol = nullptr;
   float* cval = nullptr;
   if (cc) {
@@ -1730,7 +1840,8 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
     kern::Operands op = tile_operands(p, arp, 0, p->A.col_idx, avals, p->B.row_ptr, p->B.col_idx,
                                       p->B.vals, bidx);
     tm.tile = (int)t;
-    ST_TRY(tile_numeric(p, op, T.r1 - T.r0, w, crp + T.r0, ccol, cval, 0, s, tm));
+    w.products = hb[t];
+    ST_TRY(tile_numeric(p, op, T.r1 - T.r0, T.nnz1 - T.nnz0, w, crp + T.r0, ccol, cval, 0, s, tm));
   }
   tm.tile = -1;
   tm.mark(PH_TOTAL, 0, e_total0, tm.record());
@@ -1837,6 +1948,8 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
   if (p->wide) ST_TRY(ws.get_n(index_words(p), &bidx));
   kern::SplitWs split{nullptr, nullptr, 0};
   ST_TRY(alloc_split_ws(p, ws, split));
+  kern::NarrowView narrow[2];
+  ST_TRY(alloc_narrow(p, ws, max_rows, max_q, 2, narrow));
   for (int s = 0; s < 2; ++s) {
     Slot& S = slot[s];
     S = Slot{};
@@ -1845,6 +1958,7 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
     ST_TRY(ws.get_n(max_q, &S.aval));
     ST_TRY(alloc_tile_ws(p, ws, max_rows, true, S.w));
     S.w.split = split;
+    S.w.narrow = narrow[s];
     ST_TRY(ws.get_n(max_rows + 1, &S.crp));
     if (c_on_host) {
       ST_TRY(ws.get_n(max_cb, &S.ccol));
@@ -2043,6 +2157,10 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
     HIP_TRY(kern::build_window_index(brp, B.rp_type == AIRES_IDX_I64, bcol, bval, K, p->G, p->nG, bidx,
                                      index_bmax(p, bidx), sc));
   }
+  if (narrow[0].words && nt > 0) {
+    HIP_TRY(hipStreamWaitEvent(sc, ev_in[0], 0));
+    HIP_TRY(kern::narrow_prepare(brp, B.rp_type == AIRES_IDX_I64, bcol, bval, K, N, narrow[0], sc));
+  }
   int64_t base = 0;
   for (int64_t t = 0; t < nt; ++t) {
     const aires_tile& T = p->tiles[(size_t)t];
@@ -2060,7 +2178,7 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
     // running base of C.row_ptr for this tile: crp[0] = total so far
     HIP_TRY(hipMemcpyAsync(S.crp, running, sizeof(int64_t), hipMemcpyDeviceToDevice, sc));
     tm.tile = (int)t;
-    ST_TRY(tile_symbolic(p, op, k, S.w, S.crp, prod + t, sc, tm));
+    ST_TRY(tile_symbolic(p, op, k, T.nnz1 - T.nnz0, S.w, S.crp, prod + t, sc, tm));
     HIP_TRY(hipMemcpyAsync(running, S.crp + k, sizeof(int64_t), hipMemcpyDeviceToDevice, sc));
     HIP_TRY(hipMemcpyAsync(cnt_host + 3 * t, S.crp + k, sizeof(int64_t), hipMemcpyDeviceToHost, sc));
     if (p->wide)
@@ -2132,13 +2250,20 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
         S.icap = grow;
       }
     }
+    S.w.products = cnt_host[3 * t + 2];
     if (c_on_host) {
-      ST_TRY(tile_numeric(p, op, k, S.w, S.crp, S.ccol, S.cval, base, sc, tm));
+      ST_TRY(tile_numeric(p, op, k, T.nnz1 - T.nnz0, S.w, S.crp, S.ccol, S.cval, base, sc, tm));
     } else {
-      ST_TRY(tile_numeric(p, op, k, S.w, S.crp, C_col, C_val, 0, sc, tm));
+      ST_TRY(tile_numeric(p, op, k, T.nnz1 - T.nnz0, S.w, S.crp, C_col, C_val, 0, sc, tm));
     }
     tm.tile = -1;
     HIP_TRY(hipEventRecord(ev_done[(size_t)t], sc));
+    // The next copy in goes before this tile's copy out: where the runtime
+    // has put the two copy streams on one hardware queue, it would otherwise
+    // wait for the whole copy out, past the end of the next tile's products.
+    // (Segments that the host packs or reads first would hold up the copy out.)
+    const bool in_first = !maxfill && !file;
+    if (in_first && t + 2 < nt) ST_TRY(issue_h2d(t + 2));
     // Phase III for this tile
     if (c_on_host) {
       HIP_TRY(hipStreamWaitEvent(sd, ev_done[(size_t)t], 0));
@@ -2161,7 +2286,7 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
       HIP_TRY(hipMemcpyAsync(C_rp + T.r0 + 1, S.crp + 1, sizeof(int64_t) * (size_t)k, hipMemcpyDeviceToDevice, sc));
     }
     base = end;
-    if (t + 2 < nt) ST_TRY(issue_h2d(t + 2));
+    if (!in_first && t + 2 < nt) ST_TRY(issue_h2d(t + 2));
   }
   // the pipeline ends with the last copy: join the copy streams into sc
   hipEvent_t ev_end[2];

@@ -105,9 +105,12 @@ struct WindowParams {
 // collected in long_list (count in *long_cnt) and summed by a workgroup each.
 hipError_t analyze(const Operands& op, int64_t nrows, int64_t* P, unsigned long long* total,
                    int32_t* long_cnt, int32_t* long_list, hipStream_t s);
+// nv: rows whose counts are -1 (long rows of narrow_symbolic) get the
+// popcount of their bitmap (nullptr: none).
+struct NarrowView;
 hipError_t bin_rows(const int64_t* P, int64_t nrows, const BinThresholds& th,
                     int32_t* cnt_cursor /*2*MAX_BINS zeroed*/, int32_t* binoff,
-                    int32_t* list, hipStream_t s);
+                    int32_t* list, const NarrowView* nv, int64_t* counts, hipStream_t s);
 // phase: 0 symbolic, 1 numeric.  ub_rows: host upper bound on the bin size.
 hipError_t run_bin(int kind, int phase, const Operands& op, const BinView& bv,
                    const Outputs& out, int64_t ub_rows, hipStream_t s);
@@ -127,6 +130,39 @@ hipError_t windows_symbolic(const Operands& op, const BinView& bv, const WindowP
 // wide rows: fill the window list (item_count scanned into offsets), then numeric
 hipError_t windows_numeric(const Operands& op, const BinView& bv, const WindowParams& wp,
                            const Outputs& out, int64_t ub_rows, int64_t nitems, hipStream_t s);
+// Narrow products with presence bitmaps of B's rows (narrow.hip).
+constexpr int64_t NARROW_MAX_COLS = 2048;
+constexpr int64_t NARROW_LONG = 1024;  // longer rows of A are cut into parts in the symbolic phase
+constexpr int NARROW_PART = 2048;      // entries of a part: at most nnz / NARROW_LONG parts
+constexpr int NARROW_PARTS = 32;       // parts of a split row in the numeric phase
+struct NarrowPart {
+  int32_t row, part;
+};
+struct NarrowView {
+  const uint32_t* bbm = nullptr;         // [K * words] bitmaps of B's rows
+  const unsigned char* slots = nullptr;  // [K * slot bytes] entries of B's rows (nullptr: none)
+  uint32_t* cbm = nullptr;               // [n * words] bitmaps of C's rows (per tile)
+  int32_t words = 0;                     // 4, 8, 16, 32 or 64 (0: no bitmaps)
+  int32_t lanes = 0, cap = 0, slot = 0;  // lanes per B row; entries and bytes of a slot
+  NarrowPart* parts = nullptr;           // [nnz / NARROW_LONG + 1] parts of long rows (scratch)
+  int32_t* nparts = nullptr;             // zeroed before the symbolic phase
+};
+int32_t narrow_words(int64_t N);
+// lanes, cap and slot for a B of K rows and nnz entries; false: no slots
+bool narrow_slots(int64_t N, int64_t K, int64_t nnz, NarrowView* nv);
+// writes nv.bbm and, where nv.slot > 0, nv.slots
+hipError_t narrow_prepare(const void* brp, int rpb64, const int32_t* bcol, const float* bval, int64_t K, int64_t N,
+                          const NarrowView& nv, hipStream_t s);
+// P_i, C_i's bitmap and nnz(C_i) of nrows rows with nnz entries of A
+hipError_t narrow_symbolic(const Operands& op, int64_t nrows, int64_t nnz, const NarrowView& nv, int64_t* P,
+                           int64_t* counts, unsigned long long* total, hipStream_t s);
+// numeric phase (slots needed) of the rows with 0 < P_i <= max_p
+hipError_t narrow_rows(const Operands& op, const NarrowView& nv, const int64_t* P, int64_t nrows, int64_t max_p,
+                       const Outputs& out, hipStream_t s);
+// numeric phase (slots needed) of the `rows` rows of a bin: a workgroup each,
+// or (sw) split over the dense slots, the rows beyond them a workgroup each
+hipError_t narrow_block(const Operands& op, const NarrowView& nv, const BinView& bv, const SplitWs* sw, int64_t rows,
+                        const Outputs& out, hipStream_t s);
 // The grain index of B and bmax[k] = max_j |b_kj| (NaN if the row holds one).
 hipError_t build_window_index(const void* brp, int rpb64, const int32_t* bcol, const float* bval, int64_t K,
                               int32_t G, int32_t nG, int32_t* bidx, float* bmax, hipStream_t s);

@@ -29,6 +29,7 @@
 // equal contiguous share of the terms and maps each term to its segment with
 // a segment map of its own.  Consecutive lanes read consecutive entries of a
 // B row.
+#include "device.h"
 #include "kernels.h"
 
 #include <hip/hip_runtime.h>
@@ -39,81 +40,6 @@
 namespace aires {
 namespace kern {
 namespace {
-
-constexpr int WAVE = 64;
-
-__device__ __forceinline__ int lane_id() { return __lane_id(); }
-
-// Orders LDS traffic between the lanes of one wavefront (they execute in
-// lockstep; this stops the compiler from moving LDS accesses across).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Cross-lane moves by DPP (data-parallel primitives of the GFX9 vector
-// ALU, no LDS traffic): row_shr:n = 0x110 + n shifts within rows of 16
-// lanes, row_bcast:15 = 0x142 and row_bcast:31 = 0x143 pass the last lane
-// of a row (of two rows) on to the rows that ROW_MASK enables, wave_shr:1 =
-// 0x138 shifts across the wavefront.  Lanes without a source read 0.
-template <int CTRL, int ROW_MASK, typename T>
-__device__ __forceinline__ T dpp_move(T x) {
-  static_assert(sizeof(T) == 4 || sizeof(T) == 8, "32- or 64-bit lanes");
-  if constexpr (sizeof(T) == 4) {
-    return (T)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROW_MASK, 0xf, false);
-  } else {
-    const uint64_t u = (uint64_t)x;
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROW_MASK, 0xf, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROW_MASK, 0xf, false);
-    return (T)(((uint64_t)hi << 32) | lo);
-  }
-}
-
-// Inclusive wavefront scan: Hillis-Steele steps 1, 2, 4, 8 inside rows of
-// 16 lanes, then the row totals are carried to rows 1 and 3 and to rows 2
-// and 3.  OP is + (SUM) or max (for non-negative values).
-template <bool SUM, typename T>
-__device__ __forceinline__ T wave_scan_op(T v) {
-  auto op = [](T a, T b) { return SUM ? a + b : (a > b ? a : b); };
-  v = op(v, dpp_move<0x111, 0xf>(v));
-  v = op(v, dpp_move<0x112, 0xf>(v));
-  v = op(v, dpp_move<0x114, 0xf>(v));
-  v = op(v, dpp_move<0x118, 0xf>(v));
-  v = op(v, dpp_move<0x142, 0xa>(v));
-  v = op(v, dpp_move<0x143, 0xc>(v));
-  return v;
-}
-
-template <typename T>
-__device__ __forceinline__ T wave_incl_scan(T v) {
-  return wave_scan_op<true>(v);
-}
-
-// The value of lane 63 in every lane.
-template <typename T>
-__device__ __forceinline__ T wave_last(T x) {
-  if constexpr (sizeof(T) == 4) {
-    return (T)__builtin_amdgcn_readlane((int)x, WAVE - 1);
-  } else {
-    const uint64_t u = (uint64_t)x;
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, WAVE - 1);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), WAVE - 1);
-    return (T)(((uint64_t)hi << 32) | lo);
-  }
-}
-
-template <typename T>
-__device__ __forceinline__ T wave_sum(T v) {
-  return wave_last(wave_incl_scan(v));
-}
-
-// fp32 sum over the wavefront, in every lane (butterfly over lane pairs).
-__device__ __forceinline__ float wave_sum_f32(float v) {
-#pragma unroll
-  for (int o = WAVE / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
 
 // A cooperating group: one wavefront (GROUP == 64) or the whole block.
 template <int GROUP, int BLOCK>
@@ -176,18 +102,6 @@ struct Group {
     }
   }
 };
-
-// C is written once and not read back by the kernels: stream it past the
-// caches so that B's rows stay resident there.
-template <typename T>
-__device__ __forceinline__ void store_stream(T* p, T v) {
-  __builtin_nontemporal_store(v, p);
-}
-
-template <typename RP>
-__device__ __forceinline__ int64_t ld_rp(const void* rp, int64_t i) {
-  return (int64_t)static_cast<const RP*>(rp)[i];
-}
 
 // ---------------------------------------------------------------- analyze
 
@@ -288,13 +202,21 @@ __device__ __forceinline__ void block_rows(int64_t nrows, int64_t& r0, int64_t& 
 }
 
 __global__ __launch_bounds__(256) void k_bin_count(const int64_t* P, int64_t nrows,
-                                                   const BinThresholds th, int32_t* cnt) {
+                                                   const BinThresholds th, int32_t* cnt,
+                                                   const uint32_t* cbm, int words, int64_t* counts) {
   __shared__ int32_t h[MAX_BINS];
   if (threadIdx.x < MAX_BINS) h[threadIdx.x] = 0;
   __syncthreads();
   int64_t r0, r1;
   block_rows(nrows, r0, r1);
-  for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) atomicAdd(&h[bin_of(th, P[i])], 1);
+  for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) {
+    atomicAdd(&h[bin_of(th, P[i])], 1);
+    if (cbm && counts[i] < 0) {  // a long row, whose bitmap is complete by now
+      int c = 0;
+      for (int w = 0; w < words; ++w) c += __popc(cbm[i * words + w]);
+      counts[i] = c;
+    }
+  }
   __syncthreads();
   if (threadIdx.x < th.nb && h[threadIdx.x]) atomicAdd(&cnt[threadIdx.x], h[threadIdx.x]);
 }
@@ -2022,10 +1944,11 @@ hipError_t analyze(const Operands& op, int64_t nrows, int64_t* P, unsigned long 
 }
 
 hipError_t bin_rows(const int64_t* P, int64_t nrows, const BinThresholds& th, int32_t* cnt_cursor,
-                    int32_t* binoff, int32_t* list, hipStream_t s) {
+                    int32_t* binoff, int32_t* list, const NarrowView* nv, int64_t* counts, hipStream_t s) {
   int64_t grid = nrows > 0 ? (nrows + 255) / 256 : 1;
   if (grid > 2048) grid = 2048;
-  hipLaunchKernelGGL(k_bin_count, dim3((unsigned)grid), dim3(256), 0, s, P, nrows, th, cnt_cursor);
+  hipLaunchKernelGGL(k_bin_count, dim3((unsigned)grid), dim3(256), 0, s, P, nrows, th, cnt_cursor,
+                     nv ? nv->cbm : nullptr, nv ? nv->words : 0, counts);
   hipLaunchKernelGGL(k_bin_scatter, dim3((unsigned)grid), dim3(256), 0, s, P, nrows, th, cnt_cursor,
                      cnt_cursor + MAX_BINS, binoff, list);
   return hipGetLastError();

@@ -1,0 +1,134 @@
+"""GPU parity of narrow products (N <= 2048) that read B's rows as presence
+bitmaps and fixed slots, against the oracle and against the general kernels
+(the same plan under a budget that leaves no room for bitmaps and slots)."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from workloads import CSR
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_gpu():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    return torch
+
+
+def csr_of_lengths(rng, lens, ncols, ints):
+    lens = np.minimum(np.asarray(lens), ncols)
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    col = [np.sort(rng.choice(ncols, L, replace=False)) for L in lens]
+    col = np.concatenate(col).astype(np.int32) if len(col) else np.zeros(0, np.int32)
+    val = rng.integers(-3, 4, len(col)) if ints else rng.uniform(-1, 1, len(col))
+    return CSR(len(lens), ncols, rp, col, val.astype(np.float32))
+
+
+def operands(rng, N, mean, K=700, ints=True):
+    """B: rows around `mean` entries, some empty, some far longer than a slot.
+    A: row lengths around a step (8 ... 32 entries), a window (128), the
+    symbolic phase's parts (1024, 2048) and single entries."""
+    lb = np.clip(rng.poisson(mean, K), 0, N)
+    lb[rng.choice(K, K // 20, replace=False)] = 0
+    lb[rng.choice(K, 5, replace=False)] = N
+    B = csr_of_lengths(rng, lb, N, ints)
+    # K columns only, so longer rows of A come from a taller B
+    la = np.concatenate([np.array([0, 1, 1, 2, 3, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 130, 255,
+                                   256, 257, 400, K, 1, 0, 1]), rng.integers(0, 60, 150), np.ones(40, int)])
+    return csr_of_lengths(rng, la, K, ints), B
+
+
+def run(aires, torch, A, B, rp64=(False, False), **kw):
+    def dev(M, wide):
+        return aires.to_device(CSR(M.nrows, M.ncols, M.rp.astype(np.int64 if wide else np.int32), M.col, M.val))
+    with aires.tile_plan(dev(A, rp64[0]), dev(B, rp64[1]), **kw) as plan:
+        C = aires.spgemm(plan)
+        torch.cuda.synchronize()
+        stats = aires.plan_stats(plan)
+    return C.rp.cpu().numpy(), C.col.cpu().numpy(), C.val.cpu().numpy(), stats
+
+
+WIDTHS = [(1, 1), (31, 3), (32, 5), (33, 6), (64, 6), (65, 10), (127, 12), (128, 13), (129, 14), (200, 16), (250, 25),
+          (256, 26), (500, 22), (512, 26), (513, 40), (1000, 50), (1024, 60), (2047, 70), (2048, 100), (2048, 300)]
+
+
+@pytest.mark.parametrize("N,mean", WIDTHS)
+def test_widths_and_slot_sizes(torch_gpu, N, mean):
+    """Small integer values: every sum is exact, so C equals the oracle's bit
+    for bit whatever the order."""
+    import paper_2507_02006_amd as aires
+    rng = np.random.default_rng(N * 31 + mean)
+    A, B = operands(rng, N, mean)
+    ref = oracle.spgemm(A, B)
+    print("[gpu-case] narrow N=%d mean=%d products=%d" % (N, mean, ref.products), flush=True)
+    for rp64 in ((False, False), (True, False), (False, True), (True, True)):
+        rp, col, val, st = run(aires, torch_gpu, A, B, rp64)
+        assert st["products"] == ref.products
+        assert np.array_equal(rp, ref.rp) and np.array_equal(col, ref.col) and np.array_equal(val, ref.val)
+    # rows spread over every kernel: a workgroup each, split over slots, tiles
+    for kw in (dict(wave_max_products=60, split_min_products=400), dict(wave_max_products=20, split_min_products=-1),
+               dict(wave_max_products=30, split_min_products=90, split_max_rows=3, max_tile_rows=37)):
+        rp, col, val, _ = run(aires, torch_gpu, A, B, **kw)
+        assert np.array_equal(rp, ref.rp) and np.array_equal(col, ref.col) and np.array_equal(val, ref.val)
+
+
+def test_long_rows_in_parts(torch_gpu):
+    """Rows of A around 1024 entries (one lane group or parts), 2048 and 4096
+    (the ends of a part), beside rows that touch empty rows of B only."""
+    import paper_2507_02006_amd as aires
+    rng = np.random.default_rng(3)
+    K, N = 9000, 96
+    lb = rng.poisson(9, K)
+    lb[:4000] = 0
+    B = csr_of_lengths(rng, lb, N, True)
+    lens = [1023, 1024, 1025, 2047, 2048, 2049, 4096, 4097, 8999, 9000, 5, 0, 3000]
+    A = csr_of_lengths(rng, lens, K, True)
+    empty = np.sort(rng.choice(4000, 2500, replace=False)).astype(np.int32)  # P_i = 0 with many entries
+    A = CSR(A.nrows + 1, K, np.append(A.rp, A.rp[-1] + len(empty)), np.concatenate([A.col, empty]),
+            np.concatenate([A.val, np.ones(len(empty), np.float32)]))
+    ref = oracle.spgemm(A, B)
+    for kw in ({}, dict(split_min_products=5000), dict(max_tile_rows=3)):
+        rp, col, val, st = run(aires, torch_gpu, A, B, **kw)
+        assert st["products"] == ref.products
+        assert np.array_equal(rp, ref.rp) and np.array_equal(col, ref.col) and np.array_equal(val, ref.val)
+
+
+@pytest.mark.parametrize("N,mean", [(64, 6), (500, 22), (2048, 100)])
+def test_against_the_general_kernels(torch_gpu, N, mean):
+    """The same plan with no room for bitmaps and slots: the same structure, and
+    values within the bound of two fp32 sums of n terms, gamma_n sum |a b|
+    each; infinite and NaN entries reach the same entries of C."""
+    import paper_2507_02006_amd as aires
+    rng = np.random.default_rng(N)
+    A, B = operands(rng, N, mean, ints=False)
+    A.val[rng.choice(len(A.val), 3, replace=False)] = [np.inf, -np.inf, np.nan]
+    nnz = int(oracle.spgemm(A, B).rp[-1])
+    probe_rp, probe_col, probe_val, _ = run(aires, torch_gpu, A, B)
+    dA, dB = aires.to_device(A), aires.to_device(B)
+    with aires.tile_plan(dA, dB, split_min_products=-1) as plan:
+        peak = aires.plan_info(plan).peak_bytes
+    # what the plan needs, with no room left for the bitmaps; then with room for
+    # them but not for C beside them, so that they are given back
+    room = 8 * nnz + 4096
+    for extra in (room, room + 4 * 256 * (A.nrows + B.nrows)):
+        rp, col, val, _ = run(aires, torch_gpu, A, B, (False, False), hbm_budget=peak + extra, split_min_products=-1)
+        compare(A, B, rp, col, val, probe_rp, probe_col, probe_val)
+
+
+def compare(A, B, rp, col, val, probe_rp, probe_col, probe_val):
+    assert np.array_equal(rp, probe_rp) and np.array_equal(col, probe_col)
+    fin = np.isfinite(val)
+    assert np.array_equal(fin, np.isfinite(probe_val))
+    assert np.array_equal(np.isnan(val), np.isnan(probe_val))
+    inf = ~fin & ~np.isnan(val)
+    assert np.array_equal(val[inf], probe_val[inf])
+    Aabs = CSR(A.nrows, A.ncols, A.rp, A.col, np.abs(np.nan_to_num(A.val, posinf=0, neginf=0)))
+    mag = oracle.spgemm(Aabs, CSR(B.nrows, B.ncols, B.rp, B.col, np.abs(B.val)))
+    n = np.repeat(np.diff(A.rp), np.diff(rp))
+    bound = 2 * (n + 2) * 2.0 ** -24 * mag.val
+    assert np.all(np.abs(val.astype(np.float64) - probe_val)[fin] <= bound[fin] + 1e-30)
