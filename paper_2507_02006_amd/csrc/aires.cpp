@@ -1421,7 +1421,8 @@ enum { PH_ANALYZE = 100, PH_BIN, PH_SYMBOLIC, PH_SCAN, PH_NUMERIC, PH_H2D, PH_D2
 struct TileWs {
   int64_t* P = nullptr;          // [n] intermediate products per row
   int32_t* list = nullptr;       // [n] rows grouped by bin (long-row list during analysis)
-  int32_t* binoff = nullptr;     // [MAX_BINS + 1]
+  kern::TileInfo* info = nullptr;  // products, end of C.row_ptr, windows, bin offsets (device)
+  const kern::TileInfo* host = nullptr;  // the same on the host, after the symbolic phase
   int32_t* cntcur = nullptr;     // [2 * MAX_BINS + 1] bin counts, cursors, long-row count
   int32_t* gcnt = nullptr;       // [n * nG] entries per (row, grain)     (wide)
   int64_t* icount = nullptr;     // [n + 1] windows per bin row, scanned  (wide)
@@ -1436,7 +1437,6 @@ struct TileWs {
   unsigned long long* bm_top = nullptr;
   bool item_cut = false;          // the call started with a bitmap cache (window cuts of kept rows)
   kern::NarrowView narrow;        // bitmaps and slots of a narrow product (words 0: none)
-  int64_t products = 0;           // host copy, after the symbolic phase
 };
 
 // Whether this plan's B rows may be read as presence bitmaps.
@@ -1501,7 +1501,6 @@ aires_status alloc_tile_ws(aires_plan* p, DevPool& ws, int64_t n, bool with_list
       ST_TRY(ws.get_n(n * (int64_t)p->nG, &w.gcnt));
       ST_TRY(ws.get_n(n + 1, &w.icount));
     }
-    ST_TRY(ws.get_n(kern::MAX_BINS + 1, &w.binoff));
   }
   ST_TRY(ws.get_n(2 * kern::MAX_BINS + 1, &w.cntcur));
   ST_TRY(ws.get_n(1 + kern::WIN_MAX_SLABS, &w.wcounter));
@@ -1550,40 +1549,43 @@ kern::WindowParams window_params(const aires_plan* p, const TileWs& w) {
 }
 
 // analyze + bin + symbolic + scan of one tile; counts land in crp[1..n] and
-// are scanned in place on top of crp[0].  Wide rows also get their window
-// counts scanned into w.icount.
+// are scanned in place from *base, which also goes to crp[0].  Wide rows also
+// get their window counts scanned into w.icount.  cl: what the call wants
+// cleared first, with what the tile needs clear.
 aires_status tile_symbolic(aires_plan* p, const kern::Operands& op, int64_t n, int64_t nnz, TileWs& w, int64_t* crp,
-                           unsigned long long* prod_total, hipStream_t s, Timer& tm) {
+                           const int64_t* base, kern::ClearList& cl, hipStream_t s, Timer& tm) {
   const int e0 = tm.record();
   tm.at(aires_plan::T_C0, e0);
-  HIP_TRY(hipMemsetAsync(w.cntcur, 0, sizeof(int32_t) * (2 * kern::MAX_BINS + 1), s));
+  kern::TileInfo* info = w.info;
+  cl.add(&info->products, sizeof info->products);
+  cl.add(w.cntcur, sizeof(int32_t) * (2 * kern::MAX_BINS + 1));
   if (w.narrow.words) {
     // products, patterns and counts of C's rows in one pass
-    HIP_TRY(hipMemsetAsync(w.narrow.nparts, 0, sizeof(int32_t), s));
-    HIP_TRY(kern::narrow_symbolic(op, n, nnz, w.narrow, w.P, crp + 1, prod_total, s));
+    cl.add(w.narrow.nparts, sizeof(int32_t));
+    HIP_TRY(kern::clear_words(cl, s));
+    HIP_TRY(kern::narrow_symbolic(op, n, nnz, w.narrow, w.P, crp + 1, &info->products, s));
     const int e1 = tm.record();
-    HIP_TRY(kern::bin_rows(w.P, n, p->th, w.cntcur, w.binoff, w.list, &w.narrow, crp + 1, s));
+    HIP_TRY(kern::bin_and_scan(w.P, n, p->th, w.cntcur, info->binoff, w.list, &w.narrow, crp + 1, base, &info->end,
+                               w.scan_ws, s));
     const int e2 = tm.record();
-    HIP_TRY(kern::scan_inplace(crp + 1, n, w.scan_ws, s));
-    const int e3 = tm.record();
     tm.mark(kern::KIND_DENSE_WAVE, 0, e0, e1);
     tm.mark(PH_SYMBOLIC, 0, e0, e1);
-    tm.mark(PH_BIN, 0, e1, e2);
-    tm.mark(PH_SCAN, 0, e2, e3);
+    tm.mark(PH_SCAN, 0, e1, e2);
     return AIRES_OK;
   }
-  HIP_TRY(kern::analyze(op, n, w.P, prod_total, w.cntcur + 2 * kern::MAX_BINS, w.list, s));
+  cl.add(crp + 1, sizeof(int64_t) * std::max<int64_t>(n, 0));
+  if (p->wide) cl.add(w.icount, sizeof(int64_t) * (n + 1));
+  HIP_TRY(kern::clear_words(cl, s));
+  HIP_TRY(kern::analyze(op, n, w.P, &info->products, w.cntcur + 2 * kern::MAX_BINS, w.list, s));
   const int e1 = tm.record();
-  HIP_TRY(kern::bin_rows(w.P, n, p->th, w.cntcur, w.binoff, w.list, nullptr, nullptr, s));
-  HIP_TRY(hipMemsetAsync(crp + 1, 0, sizeof(int64_t) * (size_t)std::max<int64_t>(n, 0), s));
-  if (p->wide) HIP_TRY(hipMemsetAsync(w.icount, 0, sizeof(int64_t) * (size_t)(n + 1), s));
+  HIP_TRY(kern::bin_rows(w.P, n, p->th, w.cntcur, info->binoff, w.list, nullptr, nullptr, s));
   const int e2 = tm.record();
   kern::Outputs out{};
   out.counts = crp + 1;
   for (int b = 0; b < p->th.nb; ++b) {
     const int kind = p->th.kind[b];
     if (kind == kern::KIND_EMPTY) continue;
-    kern::BinView bv{w.list, w.binoff, b};
+    kern::BinView bv{w.list, info->binoff, b};
     const int ka = tm.record();
     if (kind == kern::KIND_WINDOWS) {
       // all window bins (consecutive) as one range
@@ -1598,8 +1600,9 @@ aires_status tile_symbolic(aires_plan* p, const kern::Operands& op, int64_t n, i
     tm.mark(kind, 0, ka, tm.record());
   }
   const int e3 = tm.record();
-  HIP_TRY(kern::scan_inplace(crp + 1, n, w.scan_ws, s));
-  if (p->wide) HIP_TRY(kern::scan_inplace(w.icount + 1, n, w.scan_ws, s));
+  HIP_TRY(kern::scan_inplace(crp + 1, n, base, &info->end, w.scan_ws, s));
+  // (icount[0] is clear: the base of the windows is 0)
+  if (p->wide) HIP_TRY(kern::scan_inplace(w.icount + 1, n, w.icount, &info->windows, w.scan_ws, s));
   const int e4 = tm.record();
   tm.mark(PH_ANALYZE, 0, e0, e1);
   tm.mark(PH_BIN, 0, e1, e2);
@@ -1615,25 +1618,29 @@ aires_status tile_numeric(aires_plan* p, const kern::Operands& op, int64_t n, in
   out.ccol = ccol - c_base;
   out.cval = cval - c_base;
   // slots pay while the B rows that the products touch mostly fit them
-  const bool slots = w.narrow.words && w.narrow.slots && w.products <= nnz * w.narrow.cap;
+  const bool slots = w.narrow.words && w.narrow.slots && (int64_t)w.host->products <= nnz * w.narrow.cap;
   const int e0 = tm.record();
   for (int b = 0; b < p->th.nb; ++b) {
     const int kind = p->th.kind[b];
     if (kind == kern::KIND_EMPTY) continue;
-    kern::BinView bv{w.list, w.binoff, b};
+    kern::BinView bv{w.list, w.info->binoff, b};
+    if (kind == kern::KIND_WINDOWS)
+      while (bv.last() + 1 < p->th.nb && p->th.kind[bv.last() + 1] == kern::KIND_WINDOWS) bv.bin_last = bv.last() + 1;
+    b = bv.last();
+    // the rows of the bin, known by now: no launch for an empty one
+    const int64_t rows = w.host->binoff[bv.last() + 1] - w.host->binoff[bv.bin];
+    if (rows <= 0) continue;
     const int ka = tm.record();
     if (slots && kind == kern::KIND_DENSE_WAVE) {
       HIP_TRY(kern::narrow_rows(op, w.narrow, w.P, n, p->th.max_p[b], out, s));
     } else if (slots && (kind == kern::KIND_DENSE_BLOCK || kind == kern::KIND_DENSE_SPLIT)) {
-      HIP_TRY(kern::narrow_block(op, w.narrow, bv, kind == kern::KIND_DENSE_SPLIT ? &w.split : nullptr, n, out, s));
+      HIP_TRY(kern::narrow_block(op, w.narrow, bv, kind == kern::KIND_DENSE_SPLIT ? &w.split : nullptr, rows, out, s));
     } else if (kind == kern::KIND_WINDOWS) {
-      while (bv.last() + 1 < p->th.nb && p->th.kind[bv.last() + 1] == kern::KIND_WINDOWS) bv.bin_last = bv.last() + 1;
-      HIP_TRY(kern::windows_numeric(op, bv, window_params(p, w), out, n, w.nitems, s));
-      b = bv.last();
+      HIP_TRY(kern::windows_numeric(op, bv, window_params(p, w), out, rows, w.nitems, s));
     } else if (kind == kern::KIND_DENSE_SPLIT) {
-      HIP_TRY(kern::split_rows(1, op, bv, w.split, out, n, s));
+      HIP_TRY(kern::split_rows(1, op, bv, w.split, out, rows, s));
     } else {
-      HIP_TRY(kern::run_bin(kind, 1, op, bv, out, n, s));
+      HIP_TRY(kern::run_bin(kind, 1, op, bv, out, rows, s));
     }
     tm.mark(kind, 1, ka, tm.record());
     p->stats.numeric_launches++;
@@ -1702,17 +1709,16 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
   else ST_TRY(ws.get_n(m + 1, &crp));
   TileWs shared;
   ST_TRY(alloc_tile_ws(p, ws, max_rows, false, shared));
-  int32_t *list = nullptr, *binoff = nullptr, *gcnt = nullptr, *bidx = nullptr;
+  int32_t *list = nullptr, *gcnt = nullptr, *bidx = nullptr;
   int64_t* icount = nullptr;
-  unsigned long long* prod = nullptr;
+  kern::TileInfo* info = nullptr;
   ST_TRY(ws.get_n(m, &list));
   // products per row for all rows: the numeric sweep of tile t reads the
   // values its symbolic sweep wrote (which rows keep their bitmaps), after
   // the symbolic sweeps of the later tiles
   int64_t* P_all = nullptr;
   ST_TRY(ws.get_n(m, &P_all));
-  ST_TRY(ws.get_n(nt * (kern::MAX_BINS + 1), &binoff));
-  ST_TRY(ws.get_n(nt, &prod));  // intermediate products of each tile
+  ST_TRY(ws.get_n(nt, &info));
   // A's values: given, or derived from its pattern (Eq. 2) into the workspace
   const float* avals = p->A.vals;
   if (p->opts.a_values == AIRES_AVALUES_SYM_NORM && p->A.nnz > 0) {
@@ -1761,7 +1767,7 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
     w.P = P_all + T.r0;
     w.item_cut = item_cut;
     w.list = list + T.r0;
-    w.binoff = binoff + t * (kern::MAX_BINS + 1);
+    w.info = info + t;
     w.narrow = narrow;
     if (narrow.words) w.narrow.cbm = narrow.cbm + T.r0 * narrow.words;
     if (p->wide) {
@@ -1776,9 +1782,10 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
     }
     return w;
   };
-  HIP_TRY(hipMemsetAsync(crp, 0, sizeof(int64_t), s));
-  HIP_TRY(hipMemsetAsync(prod, 0, sizeof(unsigned long long) * (size_t)std::max<int64_t>(nt, 1), s));
-  if (bm_cache) HIP_TRY(hipMemsetAsync(bm_top, 0, sizeof(unsigned long long), s));
+  kern::ClearList clears;  // with the first tile's
+  clears.add(crp, sizeof(int64_t));
+  if (bm_cache) clears.add(bm_top, sizeof(unsigned long long));
+  if (nt == 0) HIP_TRY(kern::clear_words(clears, s));
   if (p->wide) {
     const int ea = tm.record();
     HIP_TRY(kern::build_window_index(p->B.row_ptr, p->B.rp_type == AIRES_IDX_I64, p->B.col_idx, p->B.vals, K, p->G,
@@ -1799,38 +1806,31 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
     kern::Operands op = tile_operands(p, arp, 0, p->A.col_idx, avals, p->B.row_ptr, p->B.col_idx,
                                       p->B.vals, bidx);
     tm.tile = (int)t;
-    ST_TRY(tile_symbolic(p, op, T.r1 - T.r0, T.nnz1 - T.nnz0, w, crp + T.r0, prod + t, s, tm));
+    // C.row_ptr of the tile starts where the previous tile's ended
+    ST_TRY(tile_symbolic(p, op, T.r1 - T.r0, T.nnz1 - T.nnz0, w, crp + T.r0, crp + T.r0, clears, s, tm));
+    clears = kern::ClearList{};
   }
   tm.tile = -1;
-  // The one host synchronisation: nnz(C) (and the window count of every
-  // tile) decide the allocations.  Host buffer: [0, nt) products per tile,
-  // [nt, 2nt) C.row_ptr at each tile's end, [2nt, 3nt) windows per tile.
-  std::vector<int64_t> hostbuf(3 * (size_t)std::max<int64_t>(nt, 1));
-  int64_t* hb = hostbuf.data();
-  int64_t* hb_end = hb + nt;
-  int64_t* hb_win = hb + 2 * nt;
-  if (nt > 0) HIP_TRY(hipMemcpyAsync(hb, prod, sizeof(int64_t) * (size_t)nt, hipMemcpyDeviceToHost, s));
-  for (int64_t t = 0; t < nt; ++t) {
-    const aires_tile& T = p->tiles[(size_t)t];
-    HIP_TRY(hipMemcpyAsync(hb_end + t, crp + T.r1, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    if (p->wide)
-      HIP_TRY(hipMemcpyAsync(hb_win + t, icount + T.r0 + t + (T.r1 - T.r0), sizeof(int64_t), hipMemcpyDeviceToHost,
-                             s));
-  }
+  // The one host synchronisation: nnz(C) (and the window count and row bins
+  // of every tile) decide the allocations and the numeric launches.
+  std::vector<kern::TileInfo> host((size_t)std::max<int64_t>(nt, 1));
+  if (nt > 0)
+    HIP_TRY(hipMemcpyAsync(host.data(), info, sizeof(kern::TileInfo) * (size_t)nt, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
-  const int64_t nnz = nt > 0 ? hb_end[nt - 1] : 0;
+  const int64_t nnz = nt > 0 ? host[(size_t)nt - 1].end : 0;
   if (cc && cc->nnz_out) *cc->nnz_out = nnz;
   p->stats.host_syncs = 1;
   p->stats.nnz_c = nnz;
   for (int64_t t = 0; t < nt; ++t) {
-    p->stats.products += hb[t];
-    p->trun[(size_t)t].products = hb[t];
-    p->trun[(size_t)t].nnz_c = hb_end[t] - (t > 0 ? hb_end[t - 1] : 0);
+    const kern::TileInfo& h = host[(size_t)t];
+    p->stats.products += (int64_t)h.products;
+    p->trun[(size_t)t].products = (int64_t)h.products;
+    p->trun[(size_t)t].nnz_c = h.end - (t > 0 ? host[(size_t)t - 1].end : 0);
   }
   kern::WinItem* items = nullptr;
   std::vector<int64_t> item_base((size_t)nt + 1, 0);
   if (p->wide)
-    for (int64_t t = 0; t < nt; ++t) item_base[(size_t)t + 1] = item_base[(size_t)t] + hb_win[t];
+    for (int64_t t = 0; t < nt; ++t) item_base[(size_t)t + 1] = item_base[(size_t)t] + host[(size_t)t].windows;
   // C and the window list next to everything the call holds must fit the
   // budget; the kept bitmaps are a cache and go first if they do not
   const int64_t need = 8 * std::max<int64_t>(nnz, 1) + (int64_t)sizeof(kern::WinItem) *
@@ -1872,13 +1872,13 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
     TileWs w = tile_ws(t);
     if (p->wide) {
       w.items = items + item_base[(size_t)t];
-      w.nitems = hb_win[t];
+      w.nitems = host[(size_t)t].windows;
     }
     const void* arp = static_cast<const char*>(p->A.row_ptr) + T.r0 * sA;
     kern::Operands op = tile_operands(p, arp, 0, p->A.col_idx, avals, p->B.row_ptr, p->B.col_idx,
                                       p->B.vals, bidx);
     tm.tile = (int)t;
-    w.products = hb[t];
+    w.host = &host[(size_t)t];
     ST_TRY(tile_numeric(p, op, T.r1 - T.r0, T.nnz1 - T.nnz0, w, crp + T.r0, ccol, cval, 0, s, tm));
   }
   tm.tile = -1;
@@ -1979,10 +1979,8 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
     int64_t icap;
   } slot[2];
   int32_t* bidx = nullptr;
-  unsigned long long* prod = nullptr;
-  int64_t* running = nullptr;
-  ST_TRY(ws.get_n(nt, &prod));  // intermediate products of each tile
-  ST_TRY(ws.get_n(1, &running));
+  kern::TileInfo* info = nullptr;
+  ST_TRY(ws.get_n(nt + 1, &info));  // info[t + 1]: tile t; info[0].end = 0, the start of C.row_ptr
   if (p->wide) ST_TRY(ws.get_n(index_words(p), &bidx));
   kern::SplitWs split{nullptr, nullptr, 0};
   ST_TRY(alloc_split_ws(p, ws, split));
@@ -2029,11 +2027,12 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
     HIP_TRY(hipHostMalloc((void**)&carry_val, sizeof(float) * (size_t)max_carry, hipHostMallocDefault));
     hb.v.push_back(carry_val);
   }
-  int64_t* cnt_host = nullptr;  // pinned per-tile (running nnz, windows, products)
-  HIP_TRY(hipHostMalloc((void**)&cnt_host, sizeof(int64_t) * 3 * (size_t)std::max<int64_t>(nt, 1), hipHostMallocDefault));
-  hb.v.push_back(cnt_host);
-  HIP_TRY(hipMemsetAsync(prod, 0, sizeof(unsigned long long) * (size_t)std::max<int64_t>(nt, 1), sc));
-  HIP_TRY(hipMemsetAsync(running, 0, sizeof(int64_t), sc));
+  kern::TileInfo* info_host = nullptr;  // pinned, per tile
+  HIP_TRY(hipHostMalloc((void**)&info_host, sizeof(kern::TileInfo) * (size_t)std::max<int64_t>(nt, 1),
+                        hipHostMallocDefault));
+  hb.v.push_back(info_host);
+  kern::ClearList clears;  // with the first tile's
+  clears.add(&info->end, sizeof info->end);
 
   std::vector<hipEvent_t> evs;
   struct EvGuard {
@@ -2213,22 +2212,19 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
                                     T.nnz1 - T.nnz0, sc));
     }
     kern::Operands op = tile_operands(p, tile_rp, T.nnz0, S.acol, S.aval, brp, bcol, bval, bidx);
-    // running base of C.row_ptr for this tile: crp[0] = total so far
-    HIP_TRY(hipMemcpyAsync(S.crp, running, sizeof(int64_t), hipMemcpyDeviceToDevice, sc));
     tm.tile = (int)t;
-    ST_TRY(tile_symbolic(p, op, k, T.nnz1 - T.nnz0, S.w, S.crp, prod + t, sc, tm));
-    HIP_TRY(hipMemcpyAsync(running, S.crp + k, sizeof(int64_t), hipMemcpyDeviceToDevice, sc));
-    HIP_TRY(hipMemcpyAsync(cnt_host + 3 * t, S.crp + k, sizeof(int64_t), hipMemcpyDeviceToHost, sc));
-    if (p->wide)
-      HIP_TRY(hipMemcpyAsync(cnt_host + 3 * t + 1, S.w.icount + k, sizeof(int64_t), hipMemcpyDeviceToHost, sc));
-    HIP_TRY(hipMemcpyAsync(cnt_host + 3 * t + 2, prod + t, sizeof(int64_t), hipMemcpyDeviceToHost, sc));
+    S.w.info = info + t + 1;
+    S.w.host = info_host + t;
+    ST_TRY(tile_symbolic(p, op, k, T.nnz1 - T.nnz0, S.w, S.crp, &info[t].end, clears, sc, tm));
+    clears = kern::ClearList{};
+    HIP_TRY(hipMemcpyAsync(info_host + t, S.w.info, sizeof(kern::TileInfo), hipMemcpyDeviceToHost, sc));
     HIP_TRY(hipEventRecord(ev_cnt[(size_t)t], sc));
     HIP_TRY(hipEventSynchronize(ev_cnt[(size_t)t]));
     p->stats.host_syncs++;
-    const int64_t end = cnt_host[3 * t];
+    const int64_t end = info_host[t].end;
     const int64_t nnz_t = end - base;
     p->trun[(size_t)t].nnz_c = nnz_t;
-    p->trun[(size_t)t].products = cnt_host[3 * t + 2];
+    p->trun[(size_t)t].products = (int64_t)info_host[t].products;
     if (end > cap) {
       // The C bound was an estimate (Eq. 5 mode) and C's arrays are full:
       // move the entries so far into larger ones (by half again at least).
@@ -2277,7 +2273,7 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
       S.ccap = nnz_t;
     }
     if (p->wide) {
-      S.w.nitems = cnt_host[3 * t + 1];
+      S.w.nitems = info_host[t].windows;
       if (S.w.nitems > S.icap) {
         if (S.w.items) ws.give_back(S.w.items);
         S.w.items = nullptr;
@@ -2288,7 +2284,6 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
         S.icap = grow;
       }
     }
-    S.w.products = cnt_host[3 * t + 2];
     if (c_on_host) {
       ST_TRY(tile_numeric(p, op, k, T.nnz1 - T.nnz0, S.w, S.crp, S.ccol, S.cval, base, sc, tm));
     } else {

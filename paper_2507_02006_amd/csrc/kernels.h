@@ -166,9 +166,34 @@ hipError_t narrow_block(const Operands& op, const NarrowView& nv, const BinView&
 // The grain index of B and bmax[k] = max_j |b_kj| (NaN if the row holds one).
 hipError_t build_window_index(const void* brp, int rpb64, const int32_t* bcol, const float* bval, int64_t K,
                               int32_t G, int32_t nG, int32_t* bidx, float* bmax, hipStream_t s);
-// In-place inclusive scan of x[0..n) plus x[-1] (the base): x[i] = x[-1] + sum_{j<=i} x[j].
+// In-place inclusive scan of x[0..n) from a base: x[-1] = *base, x[i] = *base +
+// sum_{j<=i} x[j]; *end (may be nullptr) receives the last one.
 size_t scan_workspace_bytes(int64_t n);
-hipError_t scan_inplace(int64_t* x, int64_t n, void* ws, hipStream_t s);
+hipError_t scan_inplace(int64_t* x, int64_t n, const int64_t* base, int64_t* end, void* ws, hipStream_t s);
+// bin_rows, then scan_inplace of the counts x (a launch for both where the rows are few)
+hipError_t bin_and_scan(const int64_t* P, int64_t n, const BinThresholds& th, int32_t* cnt_cursor, int32_t* binoff,
+                        int32_t* list, const NarrowView* nv, int64_t* x, const int64_t* base, int64_t* end, void* ws,
+                        hipStream_t s);
+// Clears n arrays of 32-bit words in one launch.
+struct ClearList {
+  static constexpr int MAX = 8;
+  int n = 0;
+  uint32_t* p[MAX];
+  int64_t words[MAX];
+  void add(void* at, int64_t bytes) {
+    p[n] = static_cast<uint32_t*>(at);
+    words[n++] = bytes / 4;
+  }
+};
+hipError_t clear_words(const ClearList& cl, hipStream_t s);
+// What the host reads of a tile after its symbolic phase.
+struct TileInfo {
+  unsigned long long products;  // zeroed before the tile
+  int64_t end;                  // C.row_ptr at the tile's end
+  int64_t windows;              // column windows (wide products)
+  int32_t binoff[MAX_BINS + 1]; // rows per bin, scanned
+  int32_t pad;
+};
 
 // Y = act(A * W) for CSR A (m x K) and dense row-major W (ldw) and Y (ldy),
 // F columns; relu != 0 applies max(0, .) before the store.  dense != 0

@@ -1725,10 +1725,13 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_scan_reduce(const int64_t* x, in
   if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
 }
 
-// Exclusive scan of the block sums plus the base x[-1], in one block.
-__global__ __launch_bounds__(SCAN_BLOCK) void k_scan_bsums(const int64_t* x, int64_t* bsum, int64_t nb) {
+// Exclusive scan of the block sums plus the base, in one block; the base goes
+// to x[-1] and the total to *end.
+__global__ __launch_bounds__(SCAN_BLOCK) void k_scan_bsums(int64_t* x, int64_t* bsum, int64_t nb, const int64_t* base,
+                                                          int64_t* end) {
   __shared__ int64_t red[SCAN_BLOCK / WAVE];
-  int64_t carry = x[-1];
+  int64_t carry = *base;
+  const int64_t b00 = carry;
   for (int64_t b0 = 0; b0 < nb; b0 += SCAN_BLOCK) {
     const int64_t i = b0 + threadIdx.x;
     const int64_t v = (i < nb) ? bsum[i] : 0;
@@ -1736,6 +1739,10 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_scan_bsums(const int64_t* x, int
     const int64_t incl = block_incl_scan_1024(v, red, &tot);
     if (i < nb) bsum[i] = carry + incl - v;
     carry += tot;
+  }
+  if (threadIdx.x == 0) {
+    x[-1] = b00;
+    if (end) *end = carry;
   }
 }
 
@@ -1757,6 +1764,109 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_scan_apply(int64_t* x, int64_t n
     const int64_t i = b0 + r;
     run += v[r];
     if (i < n) x[i] = run;
+  }
+}
+
+// ------------------------------------------- few rows: one workgroup does it
+
+constexpr int SMALL_PER = 16;  // rows per thread
+constexpr int64_t SMALL_ROWS = (int64_t)SCAN_BLOCK * SMALL_PER;
+
+// k_bin_count and k_bin_scatter (BIN) and the three scan kernels (SCAN) for at
+// most SMALL_ROWS rows, in one workgroup: each of those launches costs more
+// than its work there (4096 rows: five launches of about 4 us each against one
+// of 7 us).  The products are read once; a thread keeps its rows' bins in a
+// register.
+template <bool BIN, bool SCAN>
+__global__ __launch_bounds__(SCAN_BLOCK) void k_small_rows(const int64_t* P, int n, const BinThresholds th,
+                                                          int32_t* binoff, int32_t* list, int64_t* x,
+                                                          const int64_t* base, int64_t* end, const uint32_t* cbm,
+                                                          int words) {
+  constexpr int NW = SCAN_BLOCK / WAVE;
+  __shared__ int32_t cnt[MAX_BINS][NW];
+  __shared__ int64_t red[NW];
+  const int t = threadIdx.x, lane = lane_id(), w = t / WAVE;
+  if constexpr (BIN) {
+    uint64_t bins = 0;  // 4 bits per row, 15: no row
+#pragma unroll
+    for (int r = 0; r < SMALL_PER; ++r) {
+      const int i = r * SCAN_BLOCK + t;
+      bins |= (uint64_t)(i < n ? bin_of(th, P[i]) : 15) << (4 * r);
+    }
+    int mine[MAX_BINS];
+#pragma unroll
+    for (int b = 0; b < MAX_BINS; ++b) {
+      mine[b] = 0;
+#pragma unroll
+      for (int r = 0; r < SMALL_PER; ++r) mine[b] += __popcll(__ballot(((bins >> (4 * r)) & 15u) == (uint64_t)b));
+      if (lane == 0) cnt[b][w] = mine[b];
+    }
+    __syncthreads();
+    if (w == 0) {
+      // starts of (bin, wavefront): two of the MAX_BINS * NW counts per lane, in order
+      static_assert(MAX_BINS * NW == 2 * WAVE, "two counts per lane");
+      int32_t* c = &cnt[0][0];
+      const int a0 = c[2 * lane], a1 = c[2 * lane + 1];
+      const int ex = wave_incl_scan(a0 + a1) - a0 - a1;
+      c[2 * lane] = ex;
+      c[2 * lane + 1] = ex + a0;
+      if ((2 * lane) % NW == 0 && 2 * lane / NW <= th.nb) binoff[2 * lane / NW] = ex;
+      if (lane == 0 && th.nb == MAX_BINS) binoff[MAX_BINS] = n;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < MAX_BINS; ++b) {
+      int at = cnt[b][w];
+#pragma unroll
+      for (int r = 0; r < SMALL_PER; ++r) {
+        const bool in = ((bins >> (4 * r)) & 15u) == (uint64_t)b;
+        const uint64_t m = __ballot(in);
+        if (in)
+          list[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
+              r * SCAN_BLOCK + t;
+        at += __popcll(m);
+      }
+    }
+  }
+  if constexpr (SCAN) {
+    int64_t v[SMALL_PER];
+    int64_t s = 0;
+#pragma unroll
+    for (int r = 0; r < SMALL_PER; ++r) {
+      const int i = t * SMALL_PER + r;
+      v[r] = i < n ? x[i] : 0;
+    }
+#pragma unroll
+    for (int r = 0; r < SMALL_PER; ++r) {
+      if (cbm && v[r] < 0) {  // a long row of narrow_symbolic
+        int c = 0;
+        for (int q = 0; q < words; ++q) c += __popc(cbm[(int64_t)(t * SMALL_PER + r) * words + q]);
+        v[r] = c;
+      }
+      s += v[r];
+    }
+    const int64_t b0 = *base;
+    int64_t tot;
+    int64_t run = block_incl_scan_1024(s, red, &tot) - s + b0;
+#pragma unroll
+    for (int r = 0; r < SMALL_PER; ++r) {
+      const int i = t * SMALL_PER + r;
+      run += v[r];
+      if (i < n) x[i] = run;
+    }
+    if (t == 0) {
+      x[-1] = b0;
+      if (end) *end = b0 + tot;
+    }
+  }
+}
+
+// Clears up to ClearList::MAX arrays of 32-bit words.
+__global__ __launch_bounds__(256) void k_clear(const ClearList cl) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int a = 0; a < cl.n; ++a) {
+    uint32_t* p = cl.p[a];
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cl.words[a]; i += stride) p[i] = 0u;
   }
 }
 
@@ -1945,6 +2055,11 @@ hipError_t analyze(const Operands& op, int64_t nrows, int64_t* P, unsigned long 
 
 hipError_t bin_rows(const int64_t* P, int64_t nrows, const BinThresholds& th, int32_t* cnt_cursor,
                     int32_t* binoff, int32_t* list, const NarrowView* nv, int64_t* counts, hipStream_t s) {
+  if (nrows > 0 && nrows <= SMALL_ROWS && !nv) {
+    hipLaunchKernelGGL((k_small_rows<true, false>), dim3(1), dim3(SCAN_BLOCK), 0, s, P, (int)nrows, th, binoff, list,
+                       nullptr, nullptr, nullptr, nullptr, 0);
+    return hipGetLastError();
+  }
   int64_t grid = nrows > 0 ? (nrows + 255) / 256 : 1;
   if (grid > 2048) grid = 2048;
   hipLaunchKernelGGL(k_bin_count, dim3((unsigned)grid), dim3(256), 0, s, P, nrows, th, cnt_cursor,
@@ -1997,12 +2112,38 @@ size_t scan_workspace_bytes(int64_t n) {
   return (size_t)(nb > 0 ? nb : 1) * sizeof(int64_t);
 }
 
-hipError_t scan_inplace(int64_t* x, int64_t n, void* ws, hipStream_t s) {
+hipError_t clear_words(const ClearList& cl, hipStream_t s) {
+  if (cl.n <= 0) return hipSuccess;
+  int64_t most = 1;
+  for (int i = 0; i < cl.n; ++i) most = std::max(most, cl.words[i]);
+  const int64_t grid = std::min<int64_t>((most + 255) / 256, 2048);
+  hipLaunchKernelGGL(k_clear, dim3((unsigned)grid), dim3(256), 0, s, cl);
+  return hipGetLastError();
+}
+
+hipError_t bin_and_scan(const int64_t* P, int64_t n, const BinThresholds& th, int32_t* cnt_cursor, int32_t* binoff,
+                        int32_t* list, const NarrowView* nv, int64_t* x, const int64_t* base, int64_t* end, void* ws,
+                        hipStream_t s) {
+  if (n > SMALL_ROWS || n <= 0) {
+    hipError_t e = bin_rows(P, n, th, cnt_cursor, binoff, list, nv, x, s);
+    return e != hipSuccess ? e : scan_inplace(x, n, base, end, ws, s);
+  }
+  hipLaunchKernelGGL((k_small_rows<true, true>), dim3(1), dim3(SCAN_BLOCK), 0, s, P, (int)n, th, binoff, list, x, base,
+                     end, nv ? nv->cbm : nullptr, nv ? nv->words : 0);
+  return hipGetLastError();
+}
+
+hipError_t scan_inplace(int64_t* x, int64_t n, const int64_t* base, int64_t* end, void* ws, hipStream_t s) {
   if (n <= 0) return hipSuccess;
+  if (n <= SMALL_ROWS) {
+    hipLaunchKernelGGL((k_small_rows<false, true>), dim3(1), dim3(SCAN_BLOCK), 0, s, nullptr, (int)n, BinThresholds{},
+                       nullptr, nullptr, x, base, end, nullptr, 0);
+    return hipGetLastError();
+  }
   const int64_t nb = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
   int64_t* bsum = static_cast<int64_t*>(ws);
   hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(SCAN_BLOCK), 0, s, x, n, bsum);
-  hipLaunchKernelGGL(k_scan_bsums, dim3(1), dim3(SCAN_BLOCK), 0, s, x, bsum, nb);
+  hipLaunchKernelGGL(k_scan_bsums, dim3(1), dim3(SCAN_BLOCK), 0, s, x, bsum, nb, base, end);
   hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(SCAN_BLOCK), 0, s, x, n, bsum);
   return hipGetLastError();
 }
