@@ -304,6 +304,8 @@ struct aires_plan {
   std::unique_ptr<FileSrc> file;   // A's entries in a file (aires_tile_plan_file)
   // kernel configuration
   kern::BinThresholds th;
+  int bitmaps = 0;                  // B's rows may be read as presence bitmaps ...
+  kern::BinThresholds th_narrow{};  // ... and slots: the bins then
   int wide = 0;
   int32_t G = 0, nG = 0;           // column grains (wide products)
   int32_t win_grains = 0, win_entries = 0, count_grains = 0, win_pool_words = 0;
@@ -333,26 +335,20 @@ struct aires_plan {
 namespace {
 
 // Presence bitmaps of B's rows pay where a row's bitmap (narrow_words(N)
-// words) is at most four times the bytes of its columns on average.
+// words) is at most 16 times the bytes of its columns on average: analysis and
+// symbolic phase of 60 K rows against 6001 columns, 30 entries a row (1 KB
+// against 120 bytes), 208 against 294 us; at 262144 rows against 512 columns,
+// 26 entries a row (64 against 104 bytes), 171 against 627 us.
 bool narrow_bitmaps_pay(const aires_csr& B) {
   return B.ncols >= 1 && B.ncols <= kern::NARROW_MAX_COLS && B.nrows > 0 && B.nnz > 0 &&
-         kern::narrow_words(B.ncols) * B.nrows <= 4 * B.nnz;
+         kern::narrow_words(B.ncols) * B.nrows <= 16 * B.nnz;
 }
 
 void bin_plan(aires_plan* p) {
   const int64_t N = p->B.ncols;
   const aires_plan_opts& o = p->opts;
   const int64_t dense_max = o.dense_max_cols > 0 ? std::min<int64_t>(o.dense_max_cols, kDenseMaxCols) : kDenseMaxCols;
-  int64_t wave_max = o.wave_max_products > 0 ? o.wave_max_products : kWaveMaxProducts;
-  if (o.wave_max_products <= 0 && narrow_bitmaps_pay(p->B)) {
-    // a wavefront's longest row at about a quarter of the mean work of the
-    // chip's 8192 wavefront slots, so that it does not outlast the launch
-    // (numeric phase, 4096 rows and 1.5 M products: 92 us at 8192, 68 at
-    // 1024; 8.4 M rows and 2.6 G products: 8.4 ms at 1024, 6.5 at 16384)
-    const int64_t tiles = p->A.mem == AIRES_MEM_DEVICE ? 1 : kStreamTiles;
-    const double products = (double)p->A.nnz * ((double)p->B.nnz / (double)p->B.nrows) / (double)tiles;
-    wave_max = (int64_t)std::min(16384.0, std::max(1024.0, products / 32768.0));
-  }
+  const int64_t wave_max = o.wave_max_products > 0 ? o.wave_max_products : kWaveMaxProducts;
   const int64_t split_min = o.split_min_products > 0   ? o.split_min_products
                             : o.split_min_products < 0 ? 0  // < 0: no split rows
                                                        : kSplitMinProducts;
@@ -415,6 +411,30 @@ void bin_plan(aires_plan* p) {
     }
   }
   th.nb = nb;
+  // bins of a narrow product read through bitmaps (not where a hash limit or
+  // a narrower dense row is asked for)
+  kern::BinThresholds& tn = p->th_narrow;
+  if (N <= dense_max && o.hash_max_products == 0 && narrow_bitmaps_pay(p->B)) {
+    p->bitmaps = 1;
+    // a wavefront's longest row at about a quarter of the mean work of the
+    // chip's 8192 wavefront slots, so that it does not outlast the launch
+    // (numeric phase, 4096 rows and 1.5 M products: 75 us at 8192, 60 at
+    // 1024; 8.4 M rows and 2.6 G products: 7.9 ms at 1024, 6.0 at 16384)
+    const int64_t tiles = p->A.mem == AIRES_MEM_DEVICE ? 1 : kStreamTiles;
+    const double products = (double)p->A.nnz * ((double)p->B.nnz / (double)p->B.nrows) / (double)tiles;
+    const int64_t wave = o.wave_max_products > 0
+                             ? o.wave_max_products
+                             : (int64_t)std::min(16384.0, std::max(1024.0, products / 32768.0));
+    auto addn = [&](int kind, int64_t maxp) { tn.kind[tn.nb] = kind; tn.max_p[tn.nb] = maxp; ++tn.nb; };
+    addn(kern::KIND_EMPTY, 0);
+    addn(kern::KIND_DENSE_WAVE, wave);
+    if (p->split) {
+      addn(kern::KIND_DENSE_BLOCK, std::max(wave, split_min));
+      addn(kern::KIND_DENSE_SPLIT, INT64_MAX);
+    } else {
+      addn(kern::KIND_DENSE_BLOCK, INT64_MAX);
+    }
+  }
 }
 
 aires_status check_csr_desc(const aires_csr* M, const char* name, bool need_vals = true) {
@@ -1437,12 +1457,8 @@ struct TileWs {
   unsigned long long* bm_top = nullptr;
   bool item_cut = false;          // the call started with a bitmap cache (window cuts of kept rows)
   kern::NarrowView narrow;        // bitmaps and slots of a narrow product (words 0: none)
+  bool rebin = false;             // they were given back: the numeric phase bins the rows again
 };
-
-// Whether this plan's B rows may be read as presence bitmaps.
-bool narrow_pays(const aires_plan* p) {
-  return p->th.nb > 1 && p->th.kind[1] == kern::KIND_DENSE_WAVE && narrow_bitmaps_pay(p->B);
-}
 
 // The bitmaps of B's rows (K) and of C's rows (rows in all), the slots of B's
 // rows and the part list of a tile of up to nnz entries are optional
@@ -1453,7 +1469,7 @@ bool narrow_pays(const aires_plan* p) {
 aires_status alloc_narrow(aires_plan* p, DevPool& ws, int64_t rows, int64_t nnz, int copies, kern::NarrowView* nv) {
   for (int i = 0; i < copies; ++i) nv[i] = kern::NarrowView{};
   // (C's arrays under Eq. 5 are an estimate that may have to grow)
-  if (!narrow_pays(p) || (copies > 1 && p->opts.c_bound == AIRES_CBOUND_PAPER_EQ5)) return AIRES_OK;
+  if (!p->bitmaps || (copies > 1 && p->opts.c_bound == AIRES_CBOUND_PAPER_EQ5)) return AIRES_OK;
   const int64_t K = p->B.nrows, words = kern::narrow_words(p->B.ncols);
   const int64_t nparts = nnz / kern::NARROW_LONG + 1;
   // (of a fixed arena, half of what is left beyond the slots of a few split rows)
@@ -1548,6 +1564,13 @@ kern::WindowParams window_params(const aires_plan* p, const TileWs& w) {
   return wp;
 }
 
+// The bins of a call: by what the slots make of a row, or the general ones
+// (up to kDenseWaveMaxN columns both have dense kinds only, and the first suit
+// the general kernels too: 1900 rows squared, numeric phase 69 against 113 us).
+const kern::BinThresholds& call_bins(const aires_plan* p, const kern::NarrowView& nv) {
+  return nv.words && (nv.slots || p->B.ncols <= kDenseWaveMaxN) ? p->th_narrow : p->th;
+}
+
 // analyze + bin + symbolic + scan of one tile; counts land in crp[1..n] and
 // are scanned in place from *base, which also goes to crp[0].  Wide rows also
 // get their window counts scanned into w.icount.  cl: what the call wants
@@ -1565,7 +1588,7 @@ aires_status tile_symbolic(aires_plan* p, const kern::Operands& op, int64_t n, i
     HIP_TRY(kern::clear_words(cl, s));
     HIP_TRY(kern::narrow_symbolic(op, n, nnz, w.narrow, w.P, crp + 1, &info->products, s));
     const int e1 = tm.record();
-    HIP_TRY(kern::bin_and_scan(w.P, n, p->th, w.cntcur, info->binoff, w.list, &w.narrow, crp + 1, base, &info->end,
+    HIP_TRY(kern::bin_and_scan(w.P, n, call_bins(p, w.narrow), w.cntcur, info->binoff, w.list, &w.narrow, crp + 1, base, &info->end,
                                w.scan_ws, s));
     const int e2 = tm.record();
     tm.mark(kern::KIND_DENSE_WAVE, 0, e0, e1);
@@ -1620,19 +1643,30 @@ aires_status tile_numeric(aires_plan* p, const kern::Operands& op, int64_t n, in
   // slots pay while the B rows that the products touch mostly fit them
   const bool slots = w.narrow.words && w.narrow.slots && (int64_t)w.host->products <= nnz * w.narrow.cap;
   const int e0 = tm.record();
-  for (int b = 0; b < p->th.nb; ++b) {
-    const int kind = p->th.kind[b];
+  const kern::BinThresholds* th = &call_bins(p, w.narrow);
+  const bool rebin = w.rebin || (th == &p->th_narrow && !slots && p->B.ncols > kDenseWaveMaxN);
+  if (rebin) {
+    // the rows were binned for the slots: bin them for the general path (how
+    // many a bin holds stays on the device; n bounds it)
+    th = &p->th;
+    kern::ClearList cl;
+    cl.add(w.cntcur, sizeof(int32_t) * (2 * kern::MAX_BINS + 1));
+    HIP_TRY(kern::clear_words(cl, s));
+    HIP_TRY(kern::bin_rows(w.P, n, *th, w.cntcur, w.info->binoff, w.list, nullptr, nullptr, s));
+  }
+  for (int b = 0; b < th->nb; ++b) {
+    const int kind = th->kind[b];
     if (kind == kern::KIND_EMPTY) continue;
     kern::BinView bv{w.list, w.info->binoff, b};
     if (kind == kern::KIND_WINDOWS)
-      while (bv.last() + 1 < p->th.nb && p->th.kind[bv.last() + 1] == kern::KIND_WINDOWS) bv.bin_last = bv.last() + 1;
+      while (bv.last() + 1 < th->nb && th->kind[bv.last() + 1] == kern::KIND_WINDOWS) bv.bin_last = bv.last() + 1;
     b = bv.last();
     // the rows of the bin, known by now: no launch for an empty one
-    const int64_t rows = w.host->binoff[bv.last() + 1] - w.host->binoff[bv.bin];
+    const int64_t rows = rebin ? n : w.host->binoff[bv.last() + 1] - w.host->binoff[bv.bin];
     if (rows <= 0) continue;
     const int ka = tm.record();
     if (slots && kind == kern::KIND_DENSE_WAVE) {
-      HIP_TRY(kern::narrow_rows(op, w.narrow, w.P, n, p->th.max_p[b], out, s));
+      HIP_TRY(kern::narrow_rows(op, w.narrow, w.P, n, th->max_p[b], out, s));
     } else if (slots && (kind == kern::KIND_DENSE_BLOCK || kind == kern::KIND_DENSE_SPLIT)) {
       HIP_TRY(kern::narrow_block(op, w.narrow, bv, kind == kern::KIND_DENSE_SPLIT ? &w.split : nullptr, rows, out, s));
     } else if (kind == kern::KIND_WINDOWS) {
@@ -1757,6 +1791,7 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
   // narrow products: the bitmaps of C's rows are one array (a tile's part
   // starts at its first row), the part list is shared by the tiles
   kern::NarrowView narrow;
+  bool rebin = false;
   int64_t max_nnz = 0;
   for (const auto& t : p->tiles) max_nnz = std::max(max_nnz, t.nnz1 - t.nnz0);
   ST_TRY(alloc_narrow(p, ws, m, max_nnz, 1, &narrow));
@@ -1842,9 +1877,10 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
     bm_cap = 0;
   }
   if (narrow.words && !ws.fits(need)) {
-    // the bitmaps of a narrow product go before C is refused too: the numeric
-    // kernels without them need only the row bins
+    // the bitmaps of a narrow product go before C is refused too: the general
+    // numeric kernels need only the row bins
     ws.give_back(const_cast<uint32_t*>(narrow.bbm));  // the first part of their block
+    rebin = &call_bins(p, narrow) != &p->th;
     narrow.words = 0;
   }
   int32_t* ccol = nullptr;
@@ -1879,6 +1915,7 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
                                       p->B.vals, bidx);
     tm.tile = (int)t;
     w.host = &host[(size_t)t];
+    w.rebin = rebin;
     ST_TRY(tile_numeric(p, op, T.r1 - T.r0, T.nnz1 - T.nnz0, w, crp + T.r0, ccol, cval, 0, s, tm));
   }
   tm.tile = -1;

@@ -131,7 +131,12 @@ hipError_t windows_symbolic(const Operands& op, const BinView& bv, const WindowP
 hipError_t windows_numeric(const Operands& op, const BinView& bv, const WindowParams& wp,
                            const Outputs& out, int64_t ub_rows, int64_t nitems, hipStream_t s);
 // Narrow products with presence bitmaps of B's rows (narrow.hip).
-constexpr int64_t NARROW_MAX_COLS = 2048;
+constexpr int64_t NARROW_MAX_COLS = 8192;  // 64 lanes of 16 bytes hold a row's bitmap
+// A wavefront's dense row takes 4 N bytes of LDS, so wide rows leave few
+// wavefronts to a CU.  Numeric phase, 60 K rows: N = 3000, 47 M products, 413
+// against 577 us of the general path; N = 6001, 47 M products, 756 against 611.
+// (N = 2500 with 10 entries a row, 64 lanes to each: 713 against 484.)
+constexpr int64_t NARROW_SLOT_COLS = 4096;
 constexpr int64_t NARROW_LONG = 1024;  // longer rows of A are cut into parts in the symbolic phase
 constexpr int NARROW_PART = 2048;      // entries of a part: at most nnz / NARROW_LONG parts
 constexpr int NARROW_PARTS = 32;       // parts of a split row in the numeric phase
@@ -142,7 +147,7 @@ struct NarrowView {
   const uint32_t* bbm = nullptr;         // [K * words] bitmaps of B's rows
   const unsigned char* slots = nullptr;  // [K * slot bytes] entries of B's rows (nullptr: none)
   uint32_t* cbm = nullptr;               // [n * words] bitmaps of C's rows (per tile)
-  int32_t words = 0;                     // 4, 8, 16, 32 or 64 (0: no bitmaps)
+  int32_t words = 0;                     // 4 ... 256, a power of two (0: no bitmaps)
   int32_t lanes = 0, cap = 0, slot = 0;  // lanes per B row; entries and bytes of a slot
   NarrowPart* parts = nullptr;           // [nnz / NARROW_LONG + 1] parts of long rows (scratch)
   int32_t* nparts = nullptr;             // zeroed before the symbolic phase

@@ -1769,14 +1769,15 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_scan_apply(int64_t* x, int64_t n
 
 // ------------------------------------------- few rows: one workgroup does it
 
-constexpr int SMALL_PER = 16;  // rows per thread
+constexpr int SMALL_PER = 8;  // rows per thread
 constexpr int64_t SMALL_ROWS = (int64_t)SCAN_BLOCK * SMALL_PER;
 
 // k_bin_count and k_bin_scatter (BIN) and the three scan kernels (SCAN) for at
-// most SMALL_ROWS rows, in one workgroup: each of those launches costs more
-// than its work there (4096 rows: five launches of about 4 us each against one
-// of 7 us).  The products are read once; a thread keeps its rows' bins in a
-// register.
+// most SMALL_ROWS rows, in one workgroup, where those launches of about 4 us
+// each cost more than their work (4096 rows: 11 us; 16384 rows, where it does
+// not pay any more: 30).  A wavefront takes an equal run of rows, 64
+// at a time; a row's bin stays in a register between the count and the
+// scatter.
 template <bool BIN, bool SCAN>
 __global__ __launch_bounds__(SCAN_BLOCK) void k_small_rows(const int64_t* P, int n, const BinThresholds th,
                                                           int32_t* binoff, int32_t* list, int64_t* x,
@@ -1785,21 +1786,28 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_small_rows(const int64_t* P, int
   constexpr int NW = SCAN_BLOCK / WAVE;
   __shared__ int32_t cnt[MAX_BINS][NW];
   __shared__ int64_t red[NW];
-  const int t = threadIdx.x, lane = lane_id(), w = t / WAVE;
+  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  const int steps = (n + SCAN_BLOCK - 1) / SCAN_BLOCK;  // of 64 rows, per wavefront
+  const int i0 = w * steps * WAVE + lane;
+  int64_t v[SMALL_PER];
+  if constexpr (SCAN) {
+#pragma unroll
+    for (int r = 0; r < SMALL_PER; ++r) v[r] = r < steps && i0 + r * WAVE < n ? x[i0 + r * WAVE] : 0;
+  }
   if constexpr (BIN) {
-    uint64_t bins = 0;  // 4 bits per row, 15: no row
+    int64_t p[SMALL_PER];
+#pragma unroll
+    for (int r = 0; r < SMALL_PER; ++r) p[r] = r < steps && i0 + r * WAVE < n ? P[i0 + r * WAVE] : -1;
+    uint32_t bins = 0;  // 4 bits per row, 15: no row
 #pragma unroll
     for (int r = 0; r < SMALL_PER; ++r) {
-      const int i = r * SCAN_BLOCK + t;
-      bins |= (uint64_t)(i < n ? bin_of(th, P[i]) : 15) << (4 * r);
+      if (r < steps) bins |= (uint32_t)(p[r] >= 0 ? bin_of(th, p[r]) : 15) << (4 * r);
     }
-    int mine[MAX_BINS];
-#pragma unroll
     for (int b = 0; b < MAX_BINS; ++b) {
-      mine[b] = 0;
-#pragma unroll
-      for (int r = 0; r < SMALL_PER; ++r) mine[b] += __popcll(__ballot(((bins >> (4 * r)) & 15u) == (uint64_t)b));
-      if (lane == 0) cnt[b][w] = mine[b];
+      int mine = 0;
+      if (b < th.nb)
+        for (int r = 0; r < steps; ++r) mine += __popcll(__ballot(((bins >> (4 * r)) & 15u) == (uint32_t)b));
+      if (lane == 0) cnt[b][w] = mine;
     }
     __syncthreads();
     if (w == 0) {
@@ -1814,47 +1822,43 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_small_rows(const int64_t* P, int
       if (lane == 0 && th.nb == MAX_BINS) binoff[MAX_BINS] = n;
     }
     __syncthreads();
-#pragma unroll
-    for (int b = 0; b < MAX_BINS; ++b) {
+    for (int b = 0; b < th.nb; ++b) {
       int at = cnt[b][w];
-#pragma unroll
-      for (int r = 0; r < SMALL_PER; ++r) {
-        const bool in = ((bins >> (4 * r)) & 15u) == (uint64_t)b;
+      for (int r = 0; r < steps; ++r) {
+        const bool in = ((bins >> (4 * r)) & 15u) == (uint32_t)b;
         const uint64_t m = __ballot(in);
         if (in)
           list[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
-              r * SCAN_BLOCK + t;
+              i0 + r * WAVE;
         at += __popcll(m);
       }
     }
   }
   if constexpr (SCAN) {
-    int64_t v[SMALL_PER];
-    int64_t s = 0;
+    int64_t carry = 0;  // the wavefront's rows so far
 #pragma unroll
     for (int r = 0; r < SMALL_PER; ++r) {
-      const int i = t * SMALL_PER + r;
-      v[r] = i < n ? x[i] : 0;
-    }
-#pragma unroll
-    for (int r = 0; r < SMALL_PER; ++r) {
+      if (r >= steps) continue;
       if (cbm && v[r] < 0) {  // a long row of narrow_symbolic
         int c = 0;
-        for (int q = 0; q < words; ++q) c += __popc(cbm[(int64_t)(t * SMALL_PER + r) * words + q]);
+        for (int q = 0; q < words; ++q) c += __popc(cbm[(int64_t)(i0 + r * WAVE) * words + q]);
         v[r] = c;
       }
-      s += v[r];
+      v[r] = wave_incl_scan(v[r]) + carry;
+      carry = wave_last(v[r]);
     }
+    if (lane == 0) red[w] = carry;
+    __syncthreads();
     const int64_t b0 = *base;
-    int64_t tot;
-    int64_t run = block_incl_scan_1024(s, red, &tot) - s + b0;
-#pragma unroll
-    for (int r = 0; r < SMALL_PER; ++r) {
-      const int i = t * SMALL_PER + r;
-      run += v[r];
-      if (i < n) x[i] = run;
+    int64_t pre = b0, tot = 0;
+    for (int i = 0; i < NW; ++i) {
+      pre += i < w ? red[i] : 0;
+      tot += red[i];
     }
-    if (t == 0) {
+#pragma unroll
+    for (int r = 0; r < SMALL_PER; ++r)
+      if (r < steps && i0 + r * WAVE < n) x[i0 + r * WAVE] = v[r] + pre;
+    if (threadIdx.x == 0) {
       x[-1] = b0;
       if (end) *end = b0 + tot;
     }

@@ -1,4 +1,4 @@
-// Narrow products (N <= 2048) on gfx950, with presence bitmaps of B's rows.
+// Narrow products (N <= 8192) on gfx950, with presence bitmaps of B's rows.
 //
 // A dense enough B row is cheaper to read as N bits than as a list of
 // columns, and the union of B rows is then an OR of registers:
@@ -89,34 +89,43 @@ __global__ __launch_bounds__(256) void k_narrow_prepare(const void* brp, const i
 
 // ---------------------------------------------------------------- symbolic
 
+// Lanes that share a row in the symbolic phase: 16, or all 64 where a bitmap
+// takes more than 16 lanes of 16 bytes (L = words / 4).
+template <int L>
+constexpr int row_lanes() {
+  return L <= 16 ? 16 : WAVE;
+}
+
 // The OR of the bitmaps of the B rows named by A entries [p0, p1), over a
-// group of 16 lanes: lane sub holds words 4 (sub % L) .. + 3 (L = words / 4
-// lanes to a bitmap, 16 / L bitmaps side by side) in acc, and the products in
-// pc.  Both are the lane's own part: reduce with group_or.
+// group of GR lanes: lane sub holds words 4 (sub % L) .. + 3 (L lanes to a
+// bitmap, GR / L bitmaps side by side) in acc, and the products in pc.  Both
+// are the lane's own part: reduce with group_or.
 template <int L>
 __device__ __forceinline__ void or_rows(const int32_t* acol, int64_t p0, int64_t p1, const uint4* bbm, uint4& acc,
                                         uint32_t& pc) {
-  constexpr int EP = 16 / L;                    // entries side by side
-  constexpr int UB = L == 1 ? 4 : L == 2 ? 2 : 1;  // batches of 16 entries in flight
-  const int sub = threadIdx.x & 15;
-  for (int64_t p = p0; p < p1; p += 16 * UB) {
+  constexpr int GR = row_lanes<L>();
+  constexpr int EP = GR / L;                       // entries side by side
+  constexpr int UB = L == 1 ? 4 : L == 2 ? 2 : 1;  // batches of GR entries in flight
+  constexpr int H = L < 8 ? L : 8;                 // loads in flight per batch
+  const int sub = threadIdx.x & (GR - 1);
+  for (int64_t p = p0; p < p1; p += GR * UB) {
     int k[UB];
 #pragma unroll
-    for (int b = 0; b < UB; ++b) k[b] = p + 16 * b + sub < p1 ? acol[p + 16 * b + sub] : -1;
+    for (int b = 0; b < UB; ++b) k[b] = p + GR * b + sub < p1 ? acol[p + GR * b + sub] : -1;
 #pragma unroll
     for (int b = 0; b < UB; ++b)
+      for (int h = 0; h < L; h += H) {
+        if (L > H && p + GR * b + h * EP >= p1) break;  // uniform over the group
+        uint4 x[H];
+        bool ok[H];
 #pragma unroll
-      for (int h = 0; h < L; h += 8) {
-        uint4 x[L < 8 ? L : 8];
-        bool ok[L < 8 ? L : 8];
-#pragma unroll
-        for (int s = 0; s < (L < 8 ? L : 8); ++s) {
-          const int kk = __shfl(k[b], (h + s) * EP + sub / L, 16);
+        for (int s = 0; s < H; ++s) {
+          const int kk = __shfl(k[b], (h + s) * EP + sub / L, GR);
           ok[s] = kk >= 0;
           x[s] = bbm[(int64_t)(ok[s] ? kk : 0) * L + sub % L];
         }
 #pragma unroll
-        for (int s = 0; s < (L < 8 ? L : 8); ++s) {
+        for (int s = 0; s < H; ++s) {
           const uint32_t m = ok[s] ? ~0u : 0u;
           x[s].x &= m; x[s].y &= m; x[s].z &= m; x[s].w &= m;
           acc.x |= x[s].x; acc.y |= x[s].y; acc.z |= x[s].z; acc.w |= x[s].w;
@@ -128,30 +137,32 @@ __device__ __forceinline__ void or_rows(const int32_t* acol, int64_t p0, int64_t
 
 template <int L>
 __device__ __forceinline__ void group_or(uint4& acc, uint32_t& pc) {
+  constexpr int GR = row_lanes<L>();
 #pragma unroll
-  for (int o = L; o < 16; o <<= 1) {
-    acc.x |= __shfl_xor(acc.x, o, 16);
-    acc.y |= __shfl_xor(acc.y, o, 16);
-    acc.z |= __shfl_xor(acc.z, o, 16);
-    acc.w |= __shfl_xor(acc.w, o, 16);
+  for (int o = L; o < GR; o <<= 1) {
+    acc.x |= __shfl_xor(acc.x, o, GR);
+    acc.y |= __shfl_xor(acc.y, o, GR);
+    acc.z |= __shfl_xor(acc.z, o, GR);
+    acc.w |= __shfl_xor(acc.w, o, GR);
   }
 #pragma unroll
-  for (int o = 1; o < 16; o <<= 1) pc += __shfl_xor(pc, o, 16);
+  for (int o = 1; o < GR; o <<= 1) pc += __shfl_xor(pc, o, GR);
 }
 
-// 16 lanes per row; rows above NARROW_LONG entries are pushed as parts of
+// A lane group per row; rows above NARROW_LONG entries are pushed as parts of
 // NARROW_PART entries for k_narrow_long, with counts[row] = -1 (k_bin_count
 // sums those rows' popcounts once every part has been added).
 template <typename RA, int L>
 __global__ __launch_bounds__(256) void k_narrow_symbolic(const Operands op, int64_t nrows, const NarrowView nv,
                                                          int64_t* P, int64_t* counts, unsigned long long* total) {
   __shared__ int64_t red[256 / WAVE];
-  const int sub = threadIdx.x & 15;
-  const int64_t nsub = (int64_t)gridDim.x * (256 / 16);
+  constexpr int GR = row_lanes<L>();
+  const int sub = threadIdx.x & (GR - 1);
+  const int64_t nsub = (int64_t)gridDim.x * (256 / GR);
   const uint4* bbm = reinterpret_cast<const uint4*>(nv.bbm);
   uint4* cbm = reinterpret_cast<uint4*>(nv.cbm);
   int64_t mine = 0;
-  for (int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 4; row < nrows; row += nsub) {
+  for (int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / GR; row < nrows; row += nsub) {
     const int64_t p0 = ld_rp<RA>(op.arp, row) - op.a_base;
     const int64_t p1 = ld_rp<RA>(op.arp, row + 1) - op.a_base;
     uint4 acc = make_uint4(0u, 0u, 0u, 0u);
@@ -171,7 +182,7 @@ __global__ __launch_bounds__(256) void k_narrow_symbolic(const Operands op, int6
     group_or<L>(acc, pc);
     int c = sub < L ? __popc(acc.x) + __popc(acc.y) + __popc(acc.z) + __popc(acc.w) : 0;
 #pragma unroll
-    for (int o = 1; o < L; o <<= 1) c += __shfl_xor(c, o, 16);
+    for (int o = 1; o < L; o <<= 1) c += __shfl_xor(c, o, GR);
     if (sub < L) cbm[row * L + sub] = acc;
     if (sub == 0) {
       counts[row] = c;
@@ -189,21 +200,21 @@ __global__ __launch_bounds__(256) void k_narrow_symbolic(const Operands op, int6
   }
 }
 
-// One part of a long row per workgroup, 16 entries at a time per group of 16
-// lanes; ORed and added into the row's bitmap and products.
+// One part of a long row per workgroup, an equal share per lane group; ORed and added into the row's bitmap and products.
 template <typename RA, int L>
 __global__ __launch_bounds__(256) void k_narrow_long(const Operands op, const NarrowView nv, int64_t* P,
                                                      unsigned long long* total) {
   constexpr int W = 4 * L;
   __shared__ uint32_t bm[W];
+  constexpr int GR = row_lanes<L>();
   __shared__ uint32_t sum;
-  const int sub = threadIdx.x & 15, sg = threadIdx.x >> 4;
+  const int sub = threadIdx.x & (GR - 1), sg = threadIdx.x / GR;
   const int n = *nv.nparts;
   for (int it = blockIdx.x; it < n; it += gridDim.x) {
     const NarrowPart pt = nv.parts[it];
     const int64_t p0 = ld_rp<RA>(op.arp, pt.row) - op.a_base;
     const int64_t p1 = ld_rp<RA>(op.arp, pt.row + 1) - op.a_base;
-    constexpr int SHARE = NARROW_PART / 16;  // entries of one group
+    constexpr int SHARE = NARROW_PART / (256 / GR);  // entries of one group
     const int64_t q0 = min(p1, p0 + (int64_t)pt.part * NARROW_PART + sg * SHARE);
     const int64_t q1 = min(p1, q0 + SHARE);
     for (int i = threadIdx.x; i < W; i += 256) bm[i] = 0u;
@@ -243,7 +254,13 @@ __device__ __forceinline__ int lanes_below(uint64_t bits) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(bits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bits, 0u));
 }
 
-// the 64 presence bits of columns [64 c, 64 c + 64): lane w holds word w
+// 64 words of a row's bitmap from word 64 i on, one per lane
+__device__ __forceinline__ uint32_t row_word(const NarrowView& nv, int64_t row, int i) {
+  const int w = 64 * i + lane_id();
+  return w < nv.words ? nv.cbm[row * nv.words + w] : 0u;
+}
+
+// the 64 presence bits of the c-th 64 columns of those words: lane w holds word w
 __device__ __forceinline__ uint64_t chunk_bits(uint32_t word, int c) {
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)word, 2 * c);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)word, 2 * c + 1);
@@ -484,8 +501,7 @@ __global__ __launch_bounds__(NARROW_WAVES* WAVE, 8) void k_narrow_rows(const Ope
       const int64_t row = r0 + i;
       const int64_t s = lane_i64(rp, i), e = lane_i64(rp, i + 1);
       int64_t o0 = lane_i64(crp, i);
-      uint32_t word = 0u;
-      if (lane < nv.words) word = nv.cbm[row * nv.words + lane];
+      uint32_t word = row_word(nv, row, 0);
       for (int64_t p = s; p < e;) {
         if (p >= w0 + WINDOW) {
           w0 = p;
@@ -496,33 +512,39 @@ __global__ __launch_bounds__(NARROW_WAVES* WAVE, 8) void k_narrow_rows(const Ope
         p = w0 + j1;
       }
       wave_sync();
-      for (int c = 0; c < Np / 64; ++c) {
-        const uint64_t bits = chunk_bits(word, c);
-        if (!bits) continue;
-        const float v = D.take(c * 64 + lane);
-        if ((bits >> lane) & 1u) {
-          const int64_t o = o0 + lanes_below(bits);
-          store_stream(&out.ccol[o], c * 64 + lane);
-          store_stream(&out.cval[o], v);
+      for (int c0 = 0; c0 < Np / 64; c0 += 32) {  // 64 words hold 32 times 64 columns
+        if (c0) word = row_word(nv, row, c0 / 32);
+        const int nc = Np / 64 - c0 < 32 ? Np / 64 - c0 : 32;
+        for (int c = 0; c < nc; ++c) {
+          const uint64_t bits = chunk_bits(word, c);
+          if (!bits) continue;
+          const int col = (c0 + c) * 64 + lane;
+          const float v = D.take(col);
+          if ((bits >> lane) & 1u) {
+            const int64_t o = o0 + lanes_below(bits);
+            store_stream(&out.ccol[o], col);
+            store_stream(&out.cval[o], v);
+          }
+          o0 += __popcll(bits);
         }
-        o0 += __popcll(bits);
       }
       wave_sync();
     }
   }
 }
 
-constexpr int NARROW_BLOCK = 512;
+// wavefronts of a k_narrow_block workgroup: eight, or four where their dense
+// rows (up to 16 KB each) would leave one workgroup to a CU otherwise
+constexpr int block_waves(int64_t N) { return N <= 2048 ? 8 : 4; }
 
 // Rows of a bin, a workgroup per row (SPLIT: per part of a row, NARROW_PARTS
 // of them, added into the row's dense slot): the wavefronts take windows of
 // entries in turn, each into dense rows of its own, added up at the end.
-template <typename RA, typename RB, int S, bool TWO, bool SPLIT>
-__global__ __launch_bounds__(NARROW_BLOCK, 8) void k_narrow_block(const Operands op, const NarrowView nv, const BinView bv,
+template <typename RA, typename RB, int S, bool TWO, bool SPLIT, int NWV>
+__global__ __launch_bounds__(NWV* WAVE, NWV) void k_narrow_block(const Operands op, const NarrowView nv, const BinView bv,
                                                                const SplitWs sw, const Outputs out) {
   extern __shared__ __align__(16) unsigned char smem[];
   using DR = DenseRows<RB, S, TWO>;
-  constexpr int NWV = NARROW_BLOCK / WAVE;
   const int N = (int)op.N, Np = padded_cols(N);
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
   const int lane = lane_id();
@@ -543,8 +565,7 @@ __global__ __launch_bounds__(NARROW_BLOCK, 8) void k_narrow_block(const Operands
       p1 = min(p1, p0 + share);
       if (p0 == p1) continue;  // uniform over the workgroup
     }
-    uint32_t word = 0u;
-    if (lane < nv.words) word = nv.cbm[row * nv.words + lane];
+    uint32_t word = row_word(nv, row, 0);
     // the wavefronts' equal shares, a window at a time
     const int64_t share = ((p1 - p0 + NWV - 1) / NWV + DR::G - 1) / DR::G * DR::G;
     const int64_t q0 = min(p1, p0 + wv * share), q1 = min(p1, q0 + share);
@@ -555,24 +576,31 @@ __global__ __launch_bounds__(NARROW_BLOCK, 8) void k_narrow_block(const Operands
     }
     __syncthreads();
     // sums over the wavefronts and groups, 64 columns to a wavefront
-    const int pc = __popc(word);
-    const int pre = wave_incl_scan(pc) - pc;
-    const int64_t o0 = SPLIT ? 0 : out.crp[row];
-    for (int c = wv; c < Np / 64; c += NWV) {
-      const uint64_t bits = chunk_bits(word, c);
-      if (!bits) continue;
-      float v = 0.f;
+    int64_t o0 = SPLIT ? 0 : out.crp[row];
+    for (int c0 = 0; c0 < Np / 64; c0 += 32) {  // 64 words hold 32 times 64 columns
+      if (c0) word = row_word(nv, row, c0 / 32);
+      const int pc = __popc(word);
+      const int incl = wave_incl_scan(pc);
+      const int pre = incl - pc;
+      const int nc = Np / 64 - c0 < 32 ? Np / 64 - c0 : 32;
+      for (int c = wv; c < nc; c += NWV) {
+        const uint64_t bits = chunk_bits(word, c);
+        if (!bits) continue;
+        const int col = (c0 + c) * 64 + lane;
+        float v = 0.f;
 #pragma unroll 2
-      for (int w = 0; w < NWV; ++w) v += DR(smem + w * per, nv, Np).take(c * 64 + lane);
-      if ((bits >> lane) & 1u) {
-        if constexpr (SPLIT) {
-          if (v != 0.f) atomicAdd(&sw.acc[d * N + c * 64 + lane], v);
-        } else {
-          const int64_t o = o0 + __builtin_amdgcn_readlane(pre, 2 * c) + lanes_below(bits);
-          store_stream(&out.ccol[o], c * 64 + lane);
-          store_stream(&out.cval[o], v);
+        for (int w = 0; w < NWV; ++w) v += DR(smem + w * per, nv, Np).take(col);
+        if ((bits >> lane) & 1u) {
+          if constexpr (SPLIT) {
+            if (v != 0.f) atomicAdd(&sw.acc[d * N + col], v);
+          } else {
+            const int64_t o = o0 + __builtin_amdgcn_readlane(pre, 2 * c) + lanes_below(bits);
+            store_stream(&out.ccol[o], col);
+            store_stream(&out.cval[o], v);
+          }
         }
       }
+      o0 += wave_last(incl);
     }
     __syncthreads();
   }
@@ -593,17 +621,19 @@ __global__ __launch_bounds__(256) void k_narrow_finish(const BinView bv, const S
   const int lane = lane_id();
   for (int64_t d = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE; d < cnt; d += nw) {
     const int64_t row = list[d];
-    uint32_t word = 0u;
-    if (lane < nv.words) word = nv.cbm[row * nv.words + lane];
     int64_t o0 = out.crp[row];
-    for (int c = 0; c < (N + 63) / 64; ++c) {
-      const uint64_t bits = chunk_bits(word, c);
-      if ((bits >> lane) & 1u) {
-        const int64_t o = o0 + lanes_below(bits);
-        store_stream(&out.ccol[o], c * 64 + lane);
-        store_stream(&out.cval[o], sw.acc[d * N + c * 64 + lane]);
+    for (int c0 = 0; c0 < padded_cols(N) / 64; c0 += 32) {
+      const uint32_t word = row_word(nv, row, c0 / 32);
+      const int nc = padded_cols(N) / 64 - c0 < 32 ? padded_cols(N) / 64 - c0 : 32;
+      for (int c = 0; c < nc; ++c) {
+        const uint64_t bits = chunk_bits(word, c);
+        if ((bits >> lane) & 1u) {
+          const int64_t o = o0 + lanes_below(bits);
+          store_stream(&out.ccol[o], (c0 + c) * 64 + lane);
+          store_stream(&out.cval[o], sw.acc[d * N + (c0 + c) * 64 + lane]);
+        }
+        o0 += __popcll(bits);
       }
-      o0 += __popcll(bits);
     }
   }
 }
@@ -613,7 +643,7 @@ __global__ __launch_bounds__(256) void k_narrow_finish(const BinView bv, const S
 template <typename RA, int L>
 hipError_t symbolic_t(const Operands& op, int64_t nrows, int64_t nnz, const NarrowView& nv, int64_t* P,
                       int64_t* counts, unsigned long long* total, hipStream_t s) {
-  int64_t grid = (nrows + 15) / 16;
+  int64_t grid = (nrows * row_lanes<L>() + 255) / 256;
   if (grid > 8192) grid = 8192;
   hipLaunchKernelGGL((k_narrow_symbolic<RA, L>), dim3((unsigned)grid), dim3(256), 0, s, op, nrows, nv, P, counts,
                      total);
@@ -631,6 +661,8 @@ hipError_t symbolic_l(const Operands& op, int64_t nrows, int64_t nnz, const Narr
     case 4: return symbolic_t<RA, 4>(op, nrows, nnz, nv, P, counts, total, s);
     case 8: return symbolic_t<RA, 8>(op, nrows, nnz, nv, P, counts, total, s);
     case 16: return symbolic_t<RA, 16>(op, nrows, nnz, nv, P, counts, total, s);
+    case 32: return symbolic_t<RA, 32>(op, nrows, nnz, nv, P, counts, total, s);
+    case 64: return symbolic_t<RA, 64>(op, nrows, nnz, nv, P, counts, total, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -669,36 +701,44 @@ hipError_t rows_t(const Operands& op, const NarrowView& nv, const int64_t* P, in
   return hipGetLastError();
 }
 
-template <typename RA, typename RB, int S, bool TWO>
-hipError_t block_t(const Operands& op, const NarrowView& nv, const BinView& bv, const SplitWs* sw, int64_t rows,
+template <typename RA, typename RB, int S, bool TWO, int NWV>
+hipError_t block_w(const Operands& op, const NarrowView& nv, const BinView& bv, const SplitWs* sw, int64_t rows,
                    const Outputs& out, hipStream_t s) {
-  const int Np = padded_cols(op.N);
-  const size_t lds = (NARROW_BLOCK / WAVE) * DenseRows<RB, S, TWO>::bytes(Np);
-  if (sw && sw->cap > 0) {
-    const int64_t cap = std::min(rows, sw->cap);
-    const int64_t cg = std::min<int64_t>((cap * op.N + 255) / 256, 4096);
-    hipLaunchKernelGGL(k_narrow_clear, dim3((unsigned)cg), dim3(256), 0, s, bv, *sw,
-                       (int32_t)op.N);
-    auto kern = k_narrow_block<RA, RB, S, TWO, true>;
-    hipError_t e = allow_lds(kern, lds);
-    if (e != hipSuccess) return e;
-    const int64_t grid = std::min(cap * NARROW_PARTS, 4 * resident_blocks(kern, NARROW_BLOCK, lds));
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NARROW_BLOCK), lds, s, op, nv, bv, *sw, out);
-    const int64_t fg = std::min<int64_t>((cap + 3) / 4, 8192);
-    hipLaunchKernelGGL(k_narrow_finish, dim3((unsigned)fg), dim3(256), 0, s, bv, *sw, nv, (int32_t)op.N, out);
-    e = hipGetLastError();
-    if (e != hipSuccess || rows <= sw->cap) return e;
+  const size_t lds = NWV * DenseRows<RB, S, TWO>::bytes(padded_cols(op.N));
+  if constexpr (NWV == 8) {
+    if (sw && sw->cap > 0) {
+      const int64_t cap = std::min(rows, sw->cap);
+      const int64_t cg = std::min<int64_t>((cap * op.N + 255) / 256, 4096);
+      hipLaunchKernelGGL(k_narrow_clear, dim3((unsigned)cg), dim3(256), 0, s, bv, *sw, (int32_t)op.N);
+      auto kern = k_narrow_block<RA, RB, S, TWO, true, NWV>;
+      hipError_t e = allow_lds(kern, lds);
+      if (e != hipSuccess) return e;
+      const int64_t grid = std::min(cap * NARROW_PARTS, 4 * resident_blocks(kern, NWV * WAVE, lds));
+      hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NWV * WAVE), lds, s, op, nv, bv, *sw, out);
+      const int64_t fg = std::min<int64_t>((cap + 3) / 4, 8192);
+      hipLaunchKernelGGL(k_narrow_finish, dim3((unsigned)fg), dim3(256), 0, s, bv, *sw, nv, (int32_t)op.N, out);
+      e = hipGetLastError();
+      if (e != hipSuccess || rows <= sw->cap) return e;
+    }
   }
   // a workgroup per row (of a split bin: the rows beyond its slots)
   BinView rest = bv;
   rest.skip = sw ? (int32_t)sw->cap : 0;
   const int64_t left = rows - rest.skip;
-  auto kern = k_narrow_block<RA, RB, S, TWO, false>;
+  auto kern = k_narrow_block<RA, RB, S, TWO, false, NWV>;
   hipError_t e = allow_lds(kern, lds);
   if (e != hipSuccess) return e;
-  const int64_t grid = std::min(left, 4 * resident_blocks(kern, NARROW_BLOCK, lds));
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NARROW_BLOCK), lds, s, op, nv, rest, SplitWs{}, out);
+  const int64_t grid = std::min(left, 4 * resident_blocks(kern, NWV * WAVE, lds));
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NWV * WAVE), lds, s, op, nv, rest, SplitWs{}, out);
   return hipGetLastError();
+}
+
+template <typename RA, typename RB, int S, bool TWO>
+hipError_t block_t(const Operands& op, const NarrowView& nv, const BinView& bv, const SplitWs* sw, int64_t rows,
+                   const Outputs& out, hipStream_t s) {
+  if constexpr (S == WAVE)  // above 2048 columns the lanes are always 64
+    if (block_waves(op.N) == 4) return block_w<RA, RB, S, TWO, 4>(op, nv, bv, nullptr, rows, out, s);
+  return block_w<RA, RB, S, TWO, 8>(op, nv, bv, sw, rows, out, s);
 }
 
 // fn<RA, RB, S, TWO>(...) for the operands' row-pointer widths and the slots
@@ -735,11 +775,13 @@ int32_t narrow_words(int64_t N) {
 // floats) stay within 8 KB.
 bool narrow_slots(int64_t N, int64_t K, int64_t nnz, NarrowView* nv) {
   nv->lanes = nv->cap = nv->slot = 0;
-  if (K <= 0 || nnz <= 0) return false;
+  if (K <= 0 || nnz <= 0 || N > NARROW_SLOT_COLS) return false;
   const double mu = (double)nnz / (double)K;
+  if (N > 2048 && mu < WAVE / 2) return false;  // 64 lanes a row from there on (see NARROW_SLOT_COLS)
   const double want = mu + 2.2 * std::sqrt(mu);
   int S = 8;
   while (S < WAVE && ((double)S < 1.25 * mu || N * (WAVE / S) > 2048)) S *= 2;
+  static_assert(4 * padded_cols(NARROW_SLOT_COLS) < GOES_ON, "column words hold every column and the spare one");
   if (want > 2.0 * S) return false;
   const int slot = ((int)std::ceil(6.0 * want) + 63) / 64 * 64;
   if ((int64_t)slot * K >= (int64_t)1 << 32) return false;  // offsets in 32 bits

@@ -1,4 +1,4 @@
-"""GPU parity of narrow products (N <= 2048) that read B's rows as presence
+"""GPU parity of narrow products (N <= 8192) that read B's rows as presence
 bitmaps and fixed slots, against the oracle and against the general kernels
 (the same plan under a budget that leaves no room for bitmaps and slots)."""
 import numpy as np
@@ -54,7 +54,8 @@ def run(aires, torch, A, B, rp64=(False, False), **kw):
 
 
 WIDTHS = [(1, 1), (31, 3), (32, 5), (33, 6), (64, 6), (65, 10), (127, 12), (128, 13), (129, 14), (200, 16), (250, 25),
-          (256, 26), (500, 22), (512, 26), (513, 40), (1000, 50), (1024, 60), (2047, 70), (2048, 100), (2048, 300)]
+          (256, 26), (500, 22), (512, 26), (513, 40), (1000, 50), (1024, 60), (2047, 70), (2048, 100), (2048, 300),
+          (2049, 30), (3000, 70), (4096, 60), (4097, 45), (6001, 60), (8192, 40), (8193, 60)]
 
 
 @pytest.mark.parametrize("N,mean", WIDTHS)
@@ -98,7 +99,7 @@ def test_long_rows_in_parts(torch_gpu):
         assert np.array_equal(rp, ref.rp) and np.array_equal(col, ref.col) and np.array_equal(val, ref.val)
 
 
-@pytest.mark.parametrize("N,mean", [(64, 6), (500, 22), (2048, 100)])
+@pytest.mark.parametrize("N,mean", [(64, 6), (500, 22), (2048, 100), (5000, 50)])
 def test_against_the_general_kernels(torch_gpu, N, mean):
     """The same plan with no room for bitmaps and slots: the same structure, and
     values within the bound of two fp32 sums of n terms, gamma_n sum |a b|
