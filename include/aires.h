@@ -191,9 +191,11 @@ typedef struct aires_plan_opts {
                                    of rows with more products than this for
                                    the numeric phase (in-core runs, within a
                                    fifth of the budget the plan leaves)    */
-    int64_t split_min_products; /* 0: default (65536), < 0: never.  Rows of
-                                   a narrow product (N <= 2048) with more
-                                   products are split over workgroups      */
+    int64_t split_min_products; /* 0: default (65536 up to 2048 columns;
+                                   up to dense_max_cols the larger of 98304
+                                   and 1/256 of the tile's products), < 0:
+                                   never.  Rows with more products are
+                                   split over workgroups                   */
     int64_t split_max_rows;     /* 0: default.  Cap on the rows given dense
                                    slots for splitting; further rows of the
                                    split bin take one workgroup each       */

@@ -74,6 +74,19 @@ constexpr int64_t kSlabMinProducts = 262144;             // rows above this many
 constexpr int64_t kWaveMaxProducts = 8192;   // rows up to this go to one wavefront
 constexpr int64_t kSplitMinProducts = 65536; // narrow rows above this are split over workgroups
 constexpr int64_t kSplitWsBytes = int64_t(256) << 20;  // their dense slots
+// Rows of a product of kDenseWaveMaxN to kDenseMaxCols columns above this many
+// products, and above 1 / kSplitShareWide of all, are split too (numeric phase):
+// a workgroup takes about 1 us per 1000 products, so a hub row alone outlasts the
+// launch where the others are light.  Numeric phase: 60 K rows x 6001, 44 M
+// products, 294 K of them in the longest row: 607 -> 524 us; 20 K rows x 8000,
+// 19 M and 184 K: 371 -> 330.  What the split costs (three launches, a pass over
+// N slots per part) is not won back where the longest row has a smaller share:
+// 16000 rows squared, 51 M and 165 K: 530 us whole and 579 split; 12000 rows
+// squared, 16 M and 72 K: 277 and 306.
+constexpr int64_t kSplitMinWide = 98304;
+constexpr int32_t kSplitShareWide = 256;
+constexpr int64_t kSplitPartWide = 16384;    // products of a part
+constexpr int64_t kSplitRowsWide = 1024;     // ... as many as this, in optional workspace
 constexpr int64_t kHashMaxProducts = 4096;   // = 8192-slot table at load <= 1/2
 constexpr int64_t kFixedWorkspace = 4 << 20; // scan partials, counters, slack
 
@@ -121,6 +134,7 @@ struct DevPool {
   hipStream_t s;
   int64_t cap;      // < 0: no limit
   int64_t used = 0;
+  int64_t optional = 0;  // of that, taken beyond what the plan counted
   struct Block { void* p; int64_t n; };
   std::vector<Block> live;
   // Arena mode (the allocation-free entry point): blocks are carved, 256-byte
@@ -313,6 +327,7 @@ struct aires_plan {
   int64_t keep_bitmap = 0;         // rows with more products keep their symbolic bitmaps (-1: none)
   int32_t slab_bin = -1;           // first window bin whose rows are split over column slabs (-1: none)
   int split = 0;                   // narrow product with a split-row bin
+  int split_wide = 0;              // ... of more columns, whose slots are optional workspace
   int64_t split_cap = 0;           // rows with dense slots for the split bin
   int64_t split_ws = 0;            // bytes of those slots
   // per-tile counts of the last call (products, nnz(C), bytes copied)
@@ -356,12 +371,13 @@ void bin_plan(aires_plan* p) {
                            : o.hash_max_products < 0 ? 0  // < 0: no hash bins
                                                      : kHashMaxProducts;
   kern::BinThresholds& th = p->th;
-  std::memset(&th, 0, sizeof th);
+  th = kern::BinThresholds{};
   int nb = 0;
   auto add = [&](int kind, int64_t maxp) { th.kind[nb] = kind; th.max_p[nb] = maxp; ++nb; };
   add(kern::KIND_EMPTY, 0);
   p->wide = 0;
   p->split = 0;
+  p->split_wide = 0;
   if (N <= std::min(kDenseWaveMaxN, dense_max)) {
     // narrow product: every row fits a dense LDS row
     add(kern::KIND_DENSE_WAVE, wave_max);
@@ -379,7 +395,18 @@ void bin_plan(aires_plan* p) {
     if (hash_max > 512) add(kern::KIND_HASH_4096, std::min<int64_t>(hash_max, 2048));
     if (hash_max > 2048) add(kern::KIND_HASH_8192, hash_max);
     if (N <= dense_max) {
-      add(kern::KIND_DENSE_BLOCK, INT64_MAX);
+      if (o.split_min_products < 0) {
+        add(kern::KIND_DENSE_BLOCK, INT64_MAX);
+      } else {
+        const int64_t from = o.split_min_products > 0 ? o.split_min_products : kSplitMinWide;
+        add(kern::KIND_DENSE_BLOCK, std::max(from, std::max<int64_t>(hash_max, 1)));
+        if (o.split_min_products == 0) {
+          th.share_bin = nb - 1;
+          th.share = kSplitShareWide;
+        }
+        add(kern::KIND_DENSE_SPLIT, INT64_MAX);
+        p->split_wide = 1;
+      }
     } else {
       // window bins, the heavy rows last in the list (processed first): cut
       // where rows start keeping their symbolic bitmaps and where their
@@ -1450,7 +1477,7 @@ struct TileWs {
   int64_t nitems = 0;            // host copy of icount[n]
   int32_t* wcounter = nullptr;   // row counters of the window kernels (shared, then one per column slab)
   void* scan_ws = nullptr;
-  kern::SplitWs split{nullptr, nullptr, 0};  // dense slots of split rows (shared by all tiles)
+  kern::SplitWs split{};  // dense slots of split rows (shared by all tiles)
   int64_t* bm_off = nullptr;     // [n * ngg] kept bitmaps of the symbolic items (wide, in-core)
   uint32_t* bm_cache = nullptr;  // shared bitmap cache (nullptr: none)
   int64_t bm_cap = 0;
@@ -1459,6 +1486,12 @@ struct TileWs {
   kern::NarrowView narrow;        // bitmaps and slots of a narrow product (words 0: none)
   bool rebin = false;             // they were given back: the numeric phase bins the rows again
 };
+
+// What optional workspace may take: the budget that the plan leaves free (of a
+// fixed arena, half of what is left beyond the slots of a few split rows).
+int64_t optional_room(const aires_plan* p, const DevPool& ws) {
+  return ws.arena ? (ws.left() - (int64_t(64) << 10)) / 2 : p->budget - p->info.peak_bytes - ws.optional;
+}
 
 // The bitmaps of B's rows (K) and of C's rows (rows in all), the slots of B's
 // rows and the part list of a tile of up to nnz entries are optional
@@ -1472,8 +1505,7 @@ aires_status alloc_narrow(aires_plan* p, DevPool& ws, int64_t rows, int64_t nnz,
   if (!p->bitmaps || (copies > 1 && p->opts.c_bound == AIRES_CBOUND_PAPER_EQ5)) return AIRES_OK;
   const int64_t K = p->B.nrows, words = kern::narrow_words(p->B.ncols);
   const int64_t nparts = nnz / kern::NARROW_LONG + 1;
-  // (of a fixed arena, half of what is left beyond the slots of a few split rows)
-  const int64_t room = ws.arena ? (ws.left() - (int64_t(64) << 10)) / 2 : p->budget - p->info.peak_bytes;
+  const int64_t room = optional_room(p, ws);
   kern::NarrowView v;
   bool slots = kern::narrow_slots(p->B.ncols, K, p->B.nnz, &v);
   auto r256 = DevPool::round256;
@@ -1488,6 +1520,7 @@ aires_status alloc_narrow(aires_plan* p, DevPool& ws, int64_t rows, int64_t nnz,
   if (!fits()) return AIRES_OK;
   void* block = nullptr;
   ST_TRY(ws.get((size_t)need, &block));
+  ws.optional += need;
   char* at = static_cast<char*>(block);
   auto carve = [&](int64_t bytes) {
     char* x = at;
@@ -1524,10 +1557,27 @@ aires_status alloc_tile_ws(aires_plan* p, DevPool& ws, int64_t n, bool with_list
   return AIRES_OK;
 }
 
-aires_status alloc_split_ws(aires_plan* p, DevPool& ws, kern::SplitWs& sw) {
-  sw = kern::SplitWs{nullptr, nullptr, 0};
-  if (!p->split) return AIRES_OK;
+aires_status alloc_split_ws(aires_plan* p, DevPool& ws, int64_t rows, kern::SplitWs& sw) {
+  sw = kern::SplitWs{};
   const int64_t N = p->B.ncols;
+  if (p->split_wide) {
+    // as many slots as rows, the default and what the plan leaves free allow;
+    // rows without one take a workgroup each
+    const int64_t nwd = (N + 31) / 32;
+    const int64_t room = std::min(optional_room(p, ws), ws.left()) - 512;
+    int64_t cap = std::min(rows, p->opts.split_max_rows > 0 ? p->opts.split_max_rows : kSplitRowsWide);
+    cap = std::min(cap, room / (4 * (nwd + N)));
+    // (Eq. 5's estimate of C may have to grow into the free budget)
+    if (cap < 1 || (p->info.a_streamed && p->opts.c_bound == AIRES_CBOUND_PAPER_EQ5)) return AIRES_OK;
+    uint32_t* block = nullptr;
+    ST_TRY(ws.get_n(cap * (nwd + N), &block));
+    ws.optional += 4 * cap * (nwd + N);
+    sw.bm = block;
+    sw.acc = reinterpret_cast<float*>(block + cap * nwd);
+    sw.cap = cap;
+    return AIRES_OK;
+  }
+  if (!p->split) return AIRES_OK;
   int64_t cap = p->split_cap;
   if (ws.arena) {
     // a fixed workspace gives slots to as many split rows as fit in what is
@@ -1540,6 +1590,16 @@ aires_status alloc_split_ws(aires_plan* p, DevPool& ws, kern::SplitWs& sw) {
   ST_TRY(ws.get_n(cap * N, &sw.acc));
   sw.cap = cap;
   return AIRES_OK;
+}
+
+// The slots of a tile's split rows (wide ones: with the products per row).
+kern::SplitWs split_of(const aires_plan* p, const TileWs& w) {
+  kern::SplitWs sw = w.split;
+  if (p->split_wide) {
+    sw.P = w.P;
+    sw.per_part = kSplitPartWide;
+  }
+  return sw;
 }
 
 kern::WindowParams window_params(const aires_plan* p, const TileWs& w) {
@@ -1588,7 +1648,7 @@ aires_status tile_symbolic(aires_plan* p, const kern::Operands& op, int64_t n, i
     HIP_TRY(kern::clear_words(cl, s));
     HIP_TRY(kern::narrow_symbolic(op, n, nnz, w.narrow, w.P, crp + 1, &info->products, s));
     const int e1 = tm.record();
-    HIP_TRY(kern::bin_and_scan(w.P, n, call_bins(p, w.narrow), w.cntcur, info->binoff, w.list, &w.narrow, crp + 1, base, &info->end,
+    HIP_TRY(kern::bin_and_scan(w.P, n, call_bins(p, w.narrow), &info->products, w.cntcur, info->binoff, w.list, &w.narrow, crp + 1, base, &info->end,
                                w.scan_ws, s));
     const int e2 = tm.record();
     tm.mark(kern::KIND_DENSE_WAVE, 0, e0, e1);
@@ -1601,7 +1661,7 @@ aires_status tile_symbolic(aires_plan* p, const kern::Operands& op, int64_t n, i
   HIP_TRY(kern::clear_words(cl, s));
   HIP_TRY(kern::analyze(op, n, w.P, &info->products, w.cntcur + 2 * kern::MAX_BINS, w.list, s));
   const int e1 = tm.record();
-  HIP_TRY(kern::bin_rows(w.P, n, p->th, w.cntcur, info->binoff, w.list, nullptr, nullptr, s));
+  HIP_TRY(kern::bin_rows(w.P, n, p->th, &info->products, w.cntcur, info->binoff, w.list, nullptr, nullptr, s));
   const int e2 = tm.record();
   kern::Outputs out{};
   out.counts = crp + 1;
@@ -1618,6 +1678,8 @@ aires_status tile_symbolic(aires_plan* p, const kern::Operands& op, int64_t n, i
     } else if (kind == kern::KIND_DENSE_SPLIT) {
       HIP_TRY(kern::split_rows(0, op, bv, w.split, out, n, s));
     } else {
+      // (wide split rows are counted a workgroup each, with the block rows)
+      if (kind == kern::KIND_DENSE_BLOCK && p->split_wide) bv.bin_last = ++b;
       HIP_TRY(kern::run_bin(kind, 0, op, bv, out, n, s));
     }
     tm.mark(kind, 0, ka, tm.record());
@@ -1652,7 +1714,7 @@ aires_status tile_numeric(aires_plan* p, const kern::Operands& op, int64_t n, in
     kern::ClearList cl;
     cl.add(w.cntcur, sizeof(int32_t) * (2 * kern::MAX_BINS + 1));
     HIP_TRY(kern::clear_words(cl, s));
-    HIP_TRY(kern::bin_rows(w.P, n, *th, w.cntcur, w.info->binoff, w.list, nullptr, nullptr, s));
+    HIP_TRY(kern::bin_rows(w.P, n, *th, &w.info->products, w.cntcur, w.info->binoff, w.list, nullptr, nullptr, s));
   }
   for (int b = 0; b < th->nb; ++b) {
     const int kind = th->kind[b];
@@ -1672,7 +1734,7 @@ aires_status tile_numeric(aires_plan* p, const kern::Operands& op, int64_t n, in
     } else if (kind == kern::KIND_WINDOWS) {
       HIP_TRY(kern::windows_numeric(op, bv, window_params(p, w), out, rows, w.nitems, s));
     } else if (kind == kern::KIND_DENSE_SPLIT) {
-      HIP_TRY(kern::split_rows(1, op, bv, w.split, out, rows, s));
+      HIP_TRY(kern::split_rows(1, op, bv, split_of(p, w), out, rows, s));
     } else {
       HIP_TRY(kern::run_bin(kind, 1, op, bv, out, rows, s));
     }
@@ -1795,7 +1857,7 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
   int64_t max_nnz = 0;
   for (const auto& t : p->tiles) max_nnz = std::max(max_nnz, t.nnz1 - t.nnz0);
   ST_TRY(alloc_narrow(p, ws, m, max_nnz, 1, &narrow));
-  ST_TRY(alloc_split_ws(p, ws, shared.split));
+  ST_TRY(alloc_split_ws(p, ws, max_rows, shared.split));
   auto tile_ws = [&](int64_t t) {
     const aires_tile& T = p->tiles[(size_t)t];
     TileWs w = shared;
@@ -1882,6 +1944,10 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
     ws.give_back(const_cast<uint32_t*>(narrow.bbm));  // the first part of their block
     rebin = &call_bins(p, narrow) != &p->th;
     narrow.words = 0;
+  }
+  if (p->split_wide && shared.split.cap > 0 && !ws.fits(need)) {
+    ws.give_back(shared.split.bm);
+    shared.split = kern::SplitWs{};
   }
   int32_t* ccol = nullptr;
   float* cval = nullptr;
@@ -2019,8 +2085,8 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
   kern::TileInfo* info = nullptr;
   ST_TRY(ws.get_n(nt + 1, &info));  // info[t + 1]: tile t; info[0].end = 0, the start of C.row_ptr
   if (p->wide) ST_TRY(ws.get_n(index_words(p), &bidx));
-  kern::SplitWs split{nullptr, nullptr, 0};
-  ST_TRY(alloc_split_ws(p, ws, split));
+  kern::SplitWs split{};
+  ST_TRY(alloc_split_ws(p, ws, max_rows, split));
   kern::NarrowView narrow[2];
   ST_TRY(alloc_narrow(p, ws, max_rows, max_q, 2, narrow));
   for (int s = 0; s < 2; ++s) {

@@ -29,6 +29,8 @@ struct BinThresholds {
   int32_t nb;                    // number of bins
   int32_t kind[MAX_BINS];
   int64_t max_p[MAX_BINS];       // bin b holds rows with max_p[b-1] < P_i <= max_p[b]
+  int32_t share_bin = -1;        // this bin's max_p is raised to 1 / share of the tile's products
+  int32_t share = 1;
 };
 
 struct Operands {
@@ -108,7 +110,7 @@ hipError_t analyze(const Operands& op, int64_t nrows, int64_t* P, unsigned long 
 // nv: rows whose counts are -1 (long rows of narrow_symbolic) get the
 // popcount of their bitmap (nullptr: none).
 struct NarrowView;
-hipError_t bin_rows(const int64_t* P, int64_t nrows, const BinThresholds& th,
+hipError_t bin_rows(const int64_t* P, int64_t nrows, const BinThresholds& th, const unsigned long long* total,
                     int32_t* cnt_cursor /*2*MAX_BINS zeroed*/, int32_t* binoff,
                     int32_t* list, const NarrowView* nv, int64_t* counts, hipStream_t s);
 // phase: 0 symbolic, 1 numeric.  ub_rows: host upper bound on the bin size.
@@ -119,6 +121,8 @@ struct SplitWs {
   uint32_t* bm;
   float* acc;
   int64_t cap;
+  const int64_t* P = nullptr;  // per_part > 0: products per row, which say
+  int64_t per_part = 0;        // how many parts of so many products it has
 };
 // heavy narrow rows (phase 0 symbolic, 1 numeric); rows of the bin beyond
 // sw.cap take the one-workgroup-per-row kernel
@@ -176,7 +180,8 @@ hipError_t build_window_index(const void* brp, int rpb64, const int32_t* bcol, c
 size_t scan_workspace_bytes(int64_t n);
 hipError_t scan_inplace(int64_t* x, int64_t n, const int64_t* base, int64_t* end, void* ws, hipStream_t s);
 // bin_rows, then scan_inplace of the counts x (a launch for both where the rows are few)
-hipError_t bin_and_scan(const int64_t* P, int64_t n, const BinThresholds& th, int32_t* cnt_cursor, int32_t* binoff,
+hipError_t bin_and_scan(const int64_t* P, int64_t n, const BinThresholds& th, const unsigned long long* total,
+                        int32_t* cnt_cursor, int32_t* binoff,
                         int32_t* list, const NarrowView* nv, int64_t* x, const int64_t* base, int64_t* end, void* ws,
                         hipStream_t s);
 // Clears n arrays of 32-bit words in one launch.

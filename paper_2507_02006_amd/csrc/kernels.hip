@@ -193,6 +193,12 @@ __device__ __forceinline__ int bin_of(const BinThresholds& th, int64_t p) {
   return b;
 }
 
+// the thresholds with the one that depends on the tile's products filled in
+__device__ __forceinline__ BinThresholds with_total(BinThresholds th, const unsigned long long* total) {
+  if (th.share_bin >= 0) th.max_p[th.share_bin] = max(th.max_p[th.share_bin], (int64_t)(*total / th.share));
+  return th;
+}
+
 // Bins are counted and filled per workgroup over a contiguous range of
 // rows, with one global atomic per bin and workgroup.
 __device__ __forceinline__ void block_rows(int64_t nrows, int64_t& r0, int64_t& r1) {
@@ -201,9 +207,10 @@ __device__ __forceinline__ void block_rows(int64_t nrows, int64_t& r0, int64_t& 
   r1 = min(nrows, r0 + per);
 }
 
-__global__ __launch_bounds__(256) void k_bin_count(const int64_t* P, int64_t nrows,
-                                                   const BinThresholds th, int32_t* cnt,
+__global__ __launch_bounds__(256) void k_bin_count(const int64_t* P, int64_t nrows, const BinThresholds th0,
+                                                   const unsigned long long* total, int32_t* cnt,
                                                    const uint32_t* cbm, int words, int64_t* counts) {
+  const BinThresholds th = with_total(th0, total);
   __shared__ int32_t h[MAX_BINS];
   if (threadIdx.x < MAX_BINS) h[threadIdx.x] = 0;
   __syncthreads();
@@ -221,10 +228,11 @@ __global__ __launch_bounds__(256) void k_bin_count(const int64_t* P, int64_t nro
   if (threadIdx.x < th.nb && h[threadIdx.x]) atomicAdd(&cnt[threadIdx.x], h[threadIdx.x]);
 }
 
-__global__ __launch_bounds__(256) void k_bin_scatter(const int64_t* P, int64_t nrows,
-                                                     const BinThresholds th, const int32_t* cnt,
+__global__ __launch_bounds__(256) void k_bin_scatter(const int64_t* P, int64_t nrows, const BinThresholds th0,
+                                                     const unsigned long long* total, const int32_t* cnt,
                                                      int32_t* cursor, int32_t* binoff,
                                                      int32_t* list) {
+  const BinThresholds th = with_total(th0, total);
   __shared__ int32_t h[MAX_BINS], off[MAX_BINS + 1], base[MAX_BINS];
   if (threadIdx.x == 0) {
     int32_t s = 0;
@@ -599,7 +607,7 @@ __global__ __launch_bounds__(BLOCK) void k_dense(const Operands op, const BinVie
   g.sync();
 
   const int32_t* list = bv.list + bv.binoff[bv.bin];
-  const int64_t cnt = bv.binoff[bv.bin + 1] - bv.binoff[bv.bin];
+  const int64_t cnt = bv.binoff[bv.last() + 1] - bv.binoff[bv.bin];
   const FullRows<RB> seg{op.brp};
   for (int64_t it = (int64_t)blockIdx.x * NG + gi + bv.skip; it < cnt; it += (int64_t)gridDim.x * NG) {
     const int64_t row = list[it];
@@ -664,6 +672,7 @@ __global__ __launch_bounds__(BLOCK) void k_dense(const Operands op, const BinVie
 
 constexpr int SPLIT_BLOCK = 512;
 constexpr int SPLIT_PARTS = 32;
+constexpr int SPLIT_MAX_COLS = 16384;  // widest dense row of a workgroup
 
 template <typename RA, typename RB, bool NUM>
 __global__ __launch_bounds__(SPLIT_BLOCK) void k_split_parts(const Operands op, const BinView bv,
@@ -686,12 +695,21 @@ __global__ __launch_bounds__(SPLIT_BLOCK) void k_split_parts(const Operands op, 
   const int64_t cnt = min((int64_t)(bv.binoff[bv.bin + 1] - bv.binoff[bv.bin]), sw.cap);
   const FullRows<RB> seg{op.brp};
   for (int64_t it = blockIdx.x; it < cnt * SPLIT_PARTS; it += gridDim.x) {
-    const int64_t d = it / SPLIT_PARTS;
-    const int64_t part = it - d * SPLIT_PARTS;
+    // part by part over the rows, so that neighbouring workgroups have work
+    // where rows have fewer parts than SPLIT_PARTS
+    const int64_t part = it / cnt;
+    const int64_t d = it - part * cnt;
     const int64_t row = list[d];
     const int64_t p0 = ld_rp<RA>(op.arp, row) - op.a_base;
     const int64_t p1 = ld_rp<RA>(op.arp, row + 1) - op.a_base;
-    const int64_t len = (p1 - p0 + SPLIT_PARTS - 1) / SPLIT_PARTS;
+    int64_t parts = SPLIT_PARTS;
+    if (sw.per_part > 0) {
+      // wide dense rows: a part costs a pass over all their slots, so there
+      // are only as many as keep per_part products each
+      parts = min(parts, (sw.P[row] + sw.per_part - 1) / sw.per_part);
+      if (part >= parts) continue;  // uniform over the workgroup
+    }
+    const int64_t len = (p1 - p0 + parts - 1) / parts;
     const int64_t q0 = min(p1, p0 + part * len), q1 = min(p1, q0 + len);
     if (q0 < q1) {
       if constexpr (!NUM) {
@@ -765,6 +783,46 @@ __global__ __launch_bounds__(256) void k_split_finish(const BinView bv, const Sp
         o0 += __popcll(mask);
       }
     }
+  }
+}
+
+// The numeric finish with a workgroup per split row: a row of thousands of slots would
+// keep one wavefront for N / 64 steps one after the other.
+__global__ __launch_bounds__(256) void k_split_finish_block(const BinView bv, const SplitWs sw, int32_t N,
+                                                           const Outputs out) {
+  constexpr int NWV = 256 / WAVE;
+  __shared__ int32_t pre[SPLIT_MAX_COLS / 32];  // set bits before each word
+  __shared__ int64_t red[NWV];
+  Group<256, 256> g;
+  g.red = red;
+  const int nwd = (N + 31) / 32, t = threadIdx.x, lane = lane_id(), wv = t / WAVE;
+  const int32_t* list = bv.list + bv.binoff[bv.bin];
+  const int64_t cnt = min((int64_t)(bv.binoff[bv.bin + 1] - bv.binoff[bv.bin]), sw.cap);
+  for (int64_t d = blockIdx.x; d < cnt; d += gridDim.x) {
+    const int64_t row = list[d];
+    const uint32_t* words = sw.bm + d * nwd;
+    int32_t carry = 0;
+    for (int w0 = 0; w0 < nwd; w0 += 256) {
+      const int c = w0 + t < nwd ? __popc(words[w0 + t]) : 0;
+      int32_t tot;
+      const int32_t incl = g.incl_scan32(c, &tot);
+      if (w0 + t < nwd) pre[w0 + t] = carry + incl - c;
+      carry += tot;
+    }
+    __syncthreads();
+    const int64_t o0 = out.crp[row];
+    for (int j0 = wv * WAVE; j0 < N; j0 += 256) {
+      const int j = j0 + lane;
+      const bool present = j < N && ((words[j >> 5] >> (j & 31)) & 1u);
+      const uint64_t mask = __ballot(present);
+      const int64_t o = o0 + pre[j0 >> 5] +
+                        __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+      if (present) {
+        store_stream(&out.ccol[o], j);
+        store_stream(&out.cval[o], sw.acc[d * N + j]);
+      }
+    }
+    __syncthreads();  // pre is read before the next row's
   }
 }
 
@@ -1779,8 +1837,8 @@ constexpr int64_t SMALL_ROWS = (int64_t)SCAN_BLOCK * SMALL_PER;
 // at a time; a row's bin stays in a register between the count and the
 // scatter.
 template <bool BIN, bool SCAN>
-__global__ __launch_bounds__(SCAN_BLOCK) void k_small_rows(const int64_t* P, int n, const BinThresholds th,
-                                                          int32_t* binoff, int32_t* list, int64_t* x,
+__global__ __launch_bounds__(SCAN_BLOCK) void k_small_rows(const int64_t* P, int n, const BinThresholds th0,
+                                                          const unsigned long long* total, int32_t* binoff, int32_t* list, int64_t* x,
                                                           const int64_t* base, int64_t* end, const uint32_t* cbm,
                                                           int words) {
   constexpr int NW = SCAN_BLOCK / WAVE;
@@ -1795,6 +1853,7 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_small_rows(const int64_t* P, int
     for (int r = 0; r < SMALL_PER; ++r) v[r] = r < steps && i0 + r * WAVE < n ? x[i0 + r * WAVE] : 0;
   }
   if constexpr (BIN) {
+    const BinThresholds th = with_total(th0, total);
     int64_t p[SMALL_PER];
 #pragma unroll
     for (int r = 0; r < SMALL_PER; ++r) p[r] = r < steps && i0 + r * WAVE < n ? P[i0 + r * WAVE] : -1;
@@ -1949,6 +2008,7 @@ template <typename RA, typename RB, bool NUM>
 hipError_t split_t(const Operands& op, const BinView& bv, const SplitWs& sw, const Outputs& out,
                    int64_t ub_rows, hipStream_t s) {
   const int64_t cap_rows = std::min<int64_t>(ub_rows, sw.cap);
+  if (cap_rows <= 0) return launch_dense<RA, RB, 512, 512, NUM>(op, bv, out, ub_rows, s);  // no slots
   int64_t cg = (cap_rows * (((op.N + 31) / 32) + (NUM ? op.N : 0)) + 255) / 256;
   if (cg > 4096) cg = 4096;
   if (cg < 1) cg = 1;
@@ -1961,10 +2021,16 @@ hipError_t split_t(const Operands& op, const BinView& bv, const SplitWs& sw, con
   }
   const int64_t grid = grid_for(kern, SPLIT_BLOCK, lds, 1, cap_rows * SPLIT_PARTS);
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(SPLIT_BLOCK), lds, s, op, bv, sw);
-  int64_t fg = (cap_rows + 3) / 4;
-  if (fg > 8192) fg = 8192;
-  if (fg < 1) fg = 1;
-  hipLaunchKernelGGL((k_split_finish<NUM>), dim3((unsigned)fg), dim3(256), 0, s, bv, sw, (int32_t)op.N, out);
+  if (NUM && op.N > 2048) {
+    if (op.N > SPLIT_MAX_COLS) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_split_finish_block, dim3((unsigned)std::min<int64_t>(cap_rows, 4096)), dim3(256), 0, s,
+                       bv, sw, (int32_t)op.N, out);
+  } else {
+    int64_t fg = (cap_rows + 3) / 4;
+    if (fg > 8192) fg = 8192;
+    if (fg < 1) fg = 1;
+    hipLaunchKernelGGL((k_split_finish<NUM>), dim3((unsigned)fg), dim3(256), 0, s, bv, sw, (int32_t)op.N, out);
+  }
   // rows of the bin beyond the slots: one workgroup each
   if (ub_rows > sw.cap) {
     BinView rest = bv;
@@ -2057,18 +2123,18 @@ hipError_t analyze(const Operands& op, int64_t nrows, int64_t* P, unsigned long 
   return AIRES_DISPATCH_RP(op, analyze_t, op, nrows, P, total, long_cnt, long_list, s);
 }
 
-hipError_t bin_rows(const int64_t* P, int64_t nrows, const BinThresholds& th, int32_t* cnt_cursor,
-                    int32_t* binoff, int32_t* list, const NarrowView* nv, int64_t* counts, hipStream_t s) {
+hipError_t bin_rows(const int64_t* P, int64_t nrows, const BinThresholds& th, const unsigned long long* total,
+                    int32_t* cnt_cursor, int32_t* binoff, int32_t* list, const NarrowView* nv, int64_t* counts, hipStream_t s) {
   if (nrows > 0 && nrows <= SMALL_ROWS && !nv) {
-    hipLaunchKernelGGL((k_small_rows<true, false>), dim3(1), dim3(SCAN_BLOCK), 0, s, P, (int)nrows, th, binoff, list,
+    hipLaunchKernelGGL((k_small_rows<true, false>), dim3(1), dim3(SCAN_BLOCK), 0, s, P, (int)nrows, th, total, binoff, list,
                        nullptr, nullptr, nullptr, nullptr, 0);
     return hipGetLastError();
   }
   int64_t grid = nrows > 0 ? (nrows + 255) / 256 : 1;
   if (grid > 2048) grid = 2048;
-  hipLaunchKernelGGL(k_bin_count, dim3((unsigned)grid), dim3(256), 0, s, P, nrows, th, cnt_cursor,
+  hipLaunchKernelGGL(k_bin_count, dim3((unsigned)grid), dim3(256), 0, s, P, nrows, th, total, cnt_cursor,
                      nv ? nv->cbm : nullptr, nv ? nv->words : 0, counts);
-  hipLaunchKernelGGL(k_bin_scatter, dim3((unsigned)grid), dim3(256), 0, s, P, nrows, th, cnt_cursor,
+  hipLaunchKernelGGL(k_bin_scatter, dim3((unsigned)grid), dim3(256), 0, s, P, nrows, th, total, cnt_cursor,
                      cnt_cursor + MAX_BINS, binoff, list);
   return hipGetLastError();
 }
@@ -2125,15 +2191,16 @@ hipError_t clear_words(const ClearList& cl, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t bin_and_scan(const int64_t* P, int64_t n, const BinThresholds& th, int32_t* cnt_cursor, int32_t* binoff,
+hipError_t bin_and_scan(const int64_t* P, int64_t n, const BinThresholds& th, const unsigned long long* total,
+                        int32_t* cnt_cursor, int32_t* binoff,
                         int32_t* list, const NarrowView* nv, int64_t* x, const int64_t* base, int64_t* end, void* ws,
                         hipStream_t s) {
   if (n > SMALL_ROWS || n <= 0) {
-    hipError_t e = bin_rows(P, n, th, cnt_cursor, binoff, list, nv, x, s);
+    hipError_t e = bin_rows(P, n, th, total, cnt_cursor, binoff, list, nv, x, s);
     return e != hipSuccess ? e : scan_inplace(x, n, base, end, ws, s);
   }
-  hipLaunchKernelGGL((k_small_rows<true, true>), dim3(1), dim3(SCAN_BLOCK), 0, s, P, (int)n, th, binoff, list, x, base,
-                     end, nv ? nv->cbm : nullptr, nv ? nv->words : 0);
+  hipLaunchKernelGGL((k_small_rows<true, true>), dim3(1), dim3(SCAN_BLOCK), 0, s, P, (int)n, th, total, binoff, list,
+                     x, base, end, nv ? nv->cbm : nullptr, nv ? nv->words : 0);
   return hipGetLastError();
 }
 
@@ -2141,7 +2208,7 @@ hipError_t scan_inplace(int64_t* x, int64_t n, const int64_t* base, int64_t* end
   if (n <= 0) return hipSuccess;
   if (n <= SMALL_ROWS) {
     hipLaunchKernelGGL((k_small_rows<false, true>), dim3(1), dim3(SCAN_BLOCK), 0, s, nullptr, (int)n, BinThresholds{},
-                       nullptr, nullptr, x, base, end, nullptr, 0);
+                       nullptr, nullptr, nullptr, x, base, end, nullptr, 0);
     return hipGetLastError();
   }
   const int64_t nb = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;

@@ -133,3 +133,25 @@ def compare(A, B, rp, col, val, probe_rp, probe_col, probe_val):
     n = np.repeat(np.diff(A.rp), np.diff(rp))
     bound = 2 * (n + 2) * 2.0 ** -24 * mag.val
     assert np.all(np.abs(val.astype(np.float64) - probe_val)[fin] <= bound[fin] + 1e-30)
+
+
+@pytest.mark.parametrize("N", [2049, 5000, 12001, 16384])
+def test_wide_dense_rows_split_in_parts(torch_gpu, N):
+    """Products of 2049 to 16384 columns whose heavy rows are cut into parts of
+    16384 products (one to several), with slots for all of them, for two of
+    them and for none, in tiles, and with the bitmaps of B off (a hash limit is
+    asked for) and on; integer values, so exact."""
+    import paper_2507_02006_amd as aires
+    rng = np.random.default_rng(N)
+    K = 1500
+    B = csr_of_lengths(rng, np.clip(rng.poisson(45, K), 0, N), N, True)
+    lens = [K, 800, 400, 365, 363, 200, 90, 40, 10, 1, 0] + [5] * 60 + [1200, 700]
+    A = csr_of_lengths(rng, lens, K, True)
+    ref = oracle.spgemm(A, B)
+    print("[gpu-case] wide split N=%d" % N, flush=True)
+    base = dict(split_min_products=12000)
+    for kw in (base, dict(base, split_max_rows=2), dict(split_min_products=-1), dict(base, max_tile_rows=30),
+               dict(base, hash_max_products=4096), dict(base, hash_max_products=4096, max_tile_rows=30)):
+        rp, col, val, st = run(aires, torch_gpu, A, B, **kw)
+        assert st["products"] == ref.products
+        assert np.array_equal(rp, ref.rp) and np.array_equal(col, ref.col) and np.array_equal(val, ref.val)
