@@ -394,20 +394,16 @@ __global__ __launch_bounds__(DT_BLOCK, NT > 4 ? 3 : 4) void k_spmm_dense(
         }
       }
     };
-    // chunk k0 from the registers into LDS buffer b
-    auto write_chunk = [&](int b, int k0) {
-      // zero this thread's quarter of its row; the scatter below runs in the
-      // same wavefront after it, and LDS executes a wavefront's accesses in order
+    // chunk k0 from the registers into LDS buffer b, in two parts.
+    // A: zero this thread's quarter of its row; the scatter runs in the same
+    // wavefront after it, and LDS executes a wavefront's accesses in order.
+    // 32 entries cover the 32 columns: every entry of the row in the chunk is
+    // here.  Each is stored; one of a later chunk lands in the row's dump
+    // slot, which the products never read.
+    auto write_a = [&](int b, int k0) {
 #pragma unroll
       for (int e = 0; e < DT_K / 16; ++e)
         *reinterpret_cast<f32x4*>(&As[b][L::at(r, q * (DT_K / 4) + 4 * e)]) = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int e = 0; e < WL; ++e)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) Wt[b][L::at(wc + 16 * e + u, wk)] = w[e][u];
-      // 32 entries cover the 32 columns: every entry of the row in the
-      // chunk is here.  Each is stored; one of a later chunk lands in the
-      // row's dump slot, which the products never read.
       int n_in = 0;
 #pragma unroll
       for (int e = 0; e < DT_ENTRIES; ++e) {
@@ -420,6 +416,12 @@ __global__ __launch_bounds__(DT_BLOCK, NT > 4 ? 3 : 4) void k_spmm_dense(
       n_in += __shfl_xor(n_in, 2);
       cur += n_in;
     };
+    auto write_w = [&](int b, int e0, int e1) {
+#pragma unroll
+      for (int e = e0; e < e1; ++e)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) Wt[b][L::at(wc + 16 * e + u, wk)] = w[e][u];
+    };
     f32x16 acc[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j)
@@ -428,7 +430,8 @@ __global__ __launch_bounds__(DT_BLOCK, NT > 4 ? 3 : 4) void k_spmm_dense(
     if (nch > 0) {
       load_entries();
       load_w(0);
-      write_chunk(0, 0);
+      write_w(0, 0, WL);
+      write_a(0, 0);
       load_entries();
       load_w(DT_K);
       __syncthreads();
@@ -446,13 +449,32 @@ __global__ __launch_bounds__(DT_BLOCK, NT > 4 ? 3 : 4) void k_spmm_dense(
         for (int s = 0; s < 4; ++s)
 #pragma unroll
           for (int j = 0; j < NB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], bw[j][s], acc[j], 0, 0, 0);
+        // chunk ch+1 into the other buffer (read last in chunk ch-1, before
+        // the barrier), then the loads of chunk ch+2.  Past the last chunk
+        // both are harmless: the rows are exhausted and W's rows are out of
+        // range.  128-column tiles do this in parts between the products of
+        // the chunk's four k blocks, so that a wavefront's own staging runs
+        // under its products; with 64-column tiles, whose four workgroups per
+        // CU cover it, it comes after them (262144 x 512, parts / after:
+        // F = 256 701 / 715 us, F = 512 1365 / 1393, F = 64 237 / 221).
+        if constexpr (NT > 4) {
+          if (kb == 0) {
+            write_a(b ^ 1, (ch + 1) * DT_K);
+            load_entries();
+          } else if (kb == 8) {
+            write_w(b ^ 1, 0, WL / 2);
+          } else if (kb == 16) {
+            write_w(b ^ 1, WL / 2, WL);
+            load_w((ch + 2) * DT_K);
+          }
+        }
       }
-      // chunk ch+1 into the other buffer (read last in chunk ch-1, before the
-      // barrier), then the loads of chunk ch+2.  Past the last chunk both are
-      // harmless: the rows are exhausted and W's rows are out of range.
-      write_chunk(b ^ 1, (ch + 1) * DT_K);
-      load_entries();
-      load_w((ch + 2) * DT_K);
+      if constexpr (NT <= 4) {
+        write_w(b ^ 1, 0, WL);
+        write_a(b ^ 1, (ch + 1) * DT_K);
+        load_entries();
+        load_w((ch + 2) * DT_K);
+      }
       __syncthreads();
     }
     // register v of block j holds row 8(v/4) + 4h + v%4 of the wavefront's

@@ -198,6 +198,18 @@ def test_dense_tiles_dense_rows(torch_gpu, density):
               a_offset=1)
 
 
+@pytest.mark.parametrize("K", [1, 8, 9, 31, 32, 33, 63, 64, 65, 97])
+def test_dense_tiles_chunk_edges(torch_gpu, K):
+    """One, two and more 32-wide chunks with every kind of remainder, for
+    tiles staged after (F <= 64) and between (above) the products of a
+    chunk; the bar is check()'s summation bound."""
+    rng = np.random.default_rng(500 + K)
+    A = workloads.random_csr(rng, 131, K, 0.5)
+    for F in (64, 65, 132):
+        W = rng.uniform(-1, 1, (K, F)).astype(np.float32)
+        check(torch_gpu, A, W, relu=F == 132, rp64=F == 65, name="chunk edges K=%d F=%d" % (K, F), algo="dense_tiles")
+
+
 def test_dense_tiles_grid_loop(torch_gpu):
     """More tiles than the grid (65536 blocks): the second sweep of the
     persistent loop, checked on sampled rows and the last rows (1 075 200
