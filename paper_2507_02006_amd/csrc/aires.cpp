@@ -2557,8 +2557,8 @@ aires_status aires_spmm(const aires_csr* A, const float* W, int64_t ldw, int64_t
   if (algo == AIRES_SPMM_AUTO)
     dense = kern::spmm_dense_fits(A->ncols, ldw) && (double)A->nnz * 8.0 >= (double)A->nrows * (double)A->ncols;
   if (dense && !W && A->ncols > 0) return fail(AIRES_E_INVALID_ARG, "NULL W (dense tiles read W)");
-  HIP_TRY(kern::spmm(A->row_ptr, A->rp_type == AIRES_IDX_I64, A->col_idx, A->vals, A->nrows, A->ncols, W, ldw, F,
-                     Y, ldy, act == AIRES_ACT_RELU, dense, (hipStream_t)stream));
+  HIP_TRY(kern::spmm(A->row_ptr, A->rp_type == AIRES_IDX_I64, A->col_idx, A->vals, A->nrows, A->ncols, A->nnz, W,
+                     ldw, F, Y, ldy, act == AIRES_ACT_RELU, dense, (hipStream_t)stream));
   return AIRES_OK;
 }
 

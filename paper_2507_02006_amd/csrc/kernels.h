@@ -210,7 +210,7 @@ struct TileInfo {
 // takes the MFMA dense-tile kernel (K, ldw must satisfy spmm_dense_fits), else
 // the entry-gather kernels.
 bool spmm_dense_fits(int64_t K, int64_t ldw);
-hipError_t spmm(const void* arp, int rpa64, const int32_t* acol, const float* aval, int64_t m, int64_t K,
+hipError_t spmm(const void* arp, int rpa64, const int32_t* acol, const float* aval, int64_t m, int64_t K, int64_t nnz,
                 const float* W, int64_t ldw, int64_t F, float* Y, int64_t ldy, int relu, int dense, hipStream_t s);
 
 // a_ik = 1/sqrt(r_i r_k) (Eq. 2) for the nnz entries of rows [row0, row0 +

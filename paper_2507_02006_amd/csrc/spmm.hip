@@ -7,14 +7,17 @@
 // Entry gather (sparse A): L lanes own one entry's row of W, V columns a
 // lane, and the 64 / L lane groups of a wavefront take different entries of
 // the row of A; their partial rows are added across the groups at the end.
-// Rows with at most kHeavy entries take one wavefront each; longer rows take
-// the eight wavefronts of a workgroup, per block of 64 columns, and come
-// first in the same launch.  Dense tiles: see below.  The activation is
-// applied before the store; every element of Y is written exactly once.
+// Rows with at most kHeavy entries (more where rows are long on average) take
+// one wavefront each; longer rows take the eight wavefronts of a workgroup, per
+// block of 64 columns, and come first in the same launch.  Dense tiles: see
+// below.  The activation is applied before the store; every element of Y is
+// written exactly once.
 #include "kernels.h"
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 namespace aires {
 namespace kern {
@@ -25,6 +28,20 @@ constexpr int SPMM_BLOCK = 512;  // eight wavefronts
 // Longer rows are split over a workgroup: 128 and 512 were slower (4000 rows,
 // F = 256: 29.6 and 19.3 us against 12.8; 150 K rows: 231 and 241 against 225).
 constexpr int64_t kHeavy = 256;
+// Where rows are long on average the limit is twice the mean, as far as that is
+// no more than an even share of the work for 3072 wavefronts (about half of
+// those the chip holds): rows of like length keep the wavefronts busy by
+// themselves (20 K rows of 300 entries, F = 64 / 256: 61 / 219 us a wavefront
+// each, 100 / 373 split).
+constexpr int64_t kHeavyShare = 3072;
+// The workgroups for heavy rows look for them in groups of at most 512 rows. A
+// group's heavy rows come one after the other, so there are at least
+// kHeavyGroups groups where each can have kHeavyGroup entries (256 rows of 900
+// entries, F = 64: 877 us in one group, 11 so). More would make the light rows
+// of a small launch wait (4000 rows of 200, F = 64: 12.3 us with 8 groups,
+// 12.5 with 256, 15.5 with 512).
+constexpr int64_t kHeavyGroups = 256;
+constexpr int64_t kHeavyGroup = 1024;
 constexpr unsigned NXCD = 8;     // gfx950 hands workgroups round-robin to its 8 XCDs
 
 template <typename RP>
@@ -137,8 +154,8 @@ struct RowPart {
 // one lane per column and one entry at a time a narrow row (F = 16 ... 64)
 // left most lanes idle or moved 4 bytes a lane; L lanes of 16 bytes keep the
 // loads wide and 64 / L entries side by side.  Blocks [0, hblocks) do the
-// heavy rows: block b scans rows for them and takes column block b mod hcb
-// (64 columns) with all eight wavefronts, so that a hub row's time is divided
+// heavy rows: block b scans groups of hrows rows for them and takes column block
+// b mod hcb (64 columns) with all eight wavefronts, so that a hub row's time is divided
 // by 8 * hcb and runs beside the light rows instead of after them.  Measured
 // on symmetric R-MAT graphs against a column per lane with the heavy rows in
 // a launch of their own: 1 M rows, 17.1 M entries, F = 256: 3.65 -> 2.05 ms
@@ -147,7 +164,7 @@ template <typename RP, int L, int V>
 __global__ __launch_bounds__(SPMM_BLOCK, 6) void k_spmm_rows(const void* arp, const int32_t* acol, const float* aval,
                                                               int64_t m, const float* W, int64_t ldw, int F, float* Y,
                                                               int64_t ldy, int relu, unsigned hblocks, unsigned hcb,
-                                                              unsigned ncb, int cw) {
+                                                              int hrows, int64_t heavy, unsigned ncb, int cw) {
   constexpr int NWV = SPMM_BLOCK / WAVE;
   constexpr int LH = L < 16 ? L : 16;  // heavy rows: lanes per entry
   constexpr int HC = LH * V;           // and columns of a block
@@ -158,11 +175,11 @@ __global__ __launch_bounds__(SPMM_BLOCK, 6) void k_spmm_rows(const void* arp, co
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
   if (blockIdx.x < hblocks) {
     const int cb = (int)(blockIdx.x % hcb) * HC, ce = cb + HC < F ? cb + HC : F;
-    for (int64_t r0 = (int64_t)(blockIdx.x / hcb) * SPMM_BLOCK; r0 < m; r0 += (int64_t)(hblocks / hcb) * SPMM_BLOCK) {
+    for (int64_t r0 = (int64_t)(blockIdx.x / hcb) * hrows; r0 < m; r0 += (int64_t)(hblocks / hcb) * hrows) {
       if (threadIdx.x == 0) nfound = 0;
       __syncthreads();
       const int64_t mine = r0 + threadIdx.x;
-      if (mine < m && rp_at<RP>(arp, mine + 1) - rp_at<RP>(arp, mine) > kHeavy)
+      if ((int)threadIdx.x < hrows && mine < m && rp_at<RP>(arp, mine + 1) - rp_at<RP>(arp, mine) > heavy)
         found[atomicAdd(&nfound, 1)] = (int32_t)threadIdx.x;
       __syncthreads();
       const int n = nfound;
@@ -233,7 +250,7 @@ __global__ __launch_bounds__(SPMM_BLOCK, 6) void k_spmm_rows(const void* arp, co
         s0 = rp_at<RP>(arp, row + 2 * nw);
         s1 = rp_at<RP>(arp, row + 2 * nw + 1);
       }
-      if (p1 - p0 <= kHeavy) {
+      if (p1 - p0 <= heavy) {
         RowPart<L, V> r;
         r.start(cb, ce);
         if (p1 > p0) r.batch(kl, al, (int)(p1 - p0 < WAVE ? p1 - p0 : WAVE), W, ldw);
@@ -493,29 +510,32 @@ __global__ __launch_bounds__(DT_BLOCK, NT > 4 ? 3 : 4) void k_spmm_dense(
 }
 
 template <typename RP, int L, int V>
-hipError_t spmm_t(int relu, const void* arp, const int32_t* acol, const float* aval, int64_t m, const float* W,
-                  int64_t ldw, int F, float* Y, int64_t ldy, int64_t ncb, hipStream_t s) {
+hipError_t spmm_t(int relu, const void* arp, const int32_t* acol, const float* aval, int64_t m, int64_t nnz,
+                  const float* W, int64_t ldw, int F, float* Y, int64_t ldy, int64_t ncb, hipStream_t s) {
   constexpr int NWV = SPMM_BLOCK / WAVE;
   const int cw = (int)(((F + V - 1) / V + ncb - 1) / ncb * V);
   constexpr int HC = (L < 16 ? L : 16) * V;
   const int64_t hcb = (F + HC - 1) / HC;
-  int64_t hx = (m + SPMM_BLOCK - 1) / SPMM_BLOCK;
-  const int64_t most = hcb < 512 ? 4096 / hcb : 8;
-  if (hx > most) hx = most;
+  const int64_t heavy = std::max(kHeavy, std::min(2 * (nnz / m), nnz * ncb / kHeavyShare));
+  int64_t hx = std::max((m + SPMM_BLOCK - 1) / SPMM_BLOCK,
+                        std::min({m, nnz / kHeavyGroup, kHeavyGroups, 4 * kHeavyGroups / hcb}));
+  hx = std::min(hx, hcb < 512 ? 4096 / hcb : 8);
   hx = (hx + NXCD - 1) / NXCD * NXCD;
+  const int hrows = (int)std::min<int64_t>(SPMM_BLOCK, (m + hx - 1) / hx);
   const int64_t hblocks = hx * hcb;
   const int64_t nside = NXCD / (ncb < NXCD ? ncb : NXCD);
   int64_t g = (m + nside * NWV - 1) / (nside * NWV);
   if (g > 512) g = 512;
   hipLaunchKernelGGL((k_spmm_rows<RP, L, V>), dim3((unsigned)(hblocks + g * NXCD)), dim3(SPMM_BLOCK), 0, s, arp, acol,
-                     aval, m, W, ldw, F, Y, ldy, relu, (unsigned)hblocks, (unsigned)hcb, (unsigned)ncb, cw);
+                     aval, m, W, ldw, F, Y, ldy, relu, (unsigned)hblocks, (unsigned)hcb, hrows, heavy,
+                     (unsigned)ncb, cw);
   return hipGetLastError();
 }
 
 template <typename RP>
-hipError_t spmm_rp(int relu, const void* arp, const int32_t* acol, const float* aval, int64_t m, const float* W,
-                   int64_t ldw, int F, float* Y, int64_t ldy, hipStream_t s) {
-  if (F < 4) return spmm_t<RP, 4, 1>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, 1, s);
+hipError_t spmm_rp(int relu, const void* arp, const int32_t* acol, const float* aval, int64_t m, int64_t nnz,
+                   const float* W, int64_t ldw, int F, float* Y, int64_t ldy, hipStream_t s) {
+  if (F < 4) return spmm_t<RP, 4, 1>(relu, arp, acol, aval, m, nnz, W, ldw, F, Y, ldy, 1, s);
   // Column blocks of at most 64 vectors, a power of two of them up to the
   // number of XCDs (each XCD then gathers from a part of W's columns), and
   // two where both halves of a row are whole cache lines (1 M rows, F = 256:
@@ -527,12 +547,12 @@ hipError_t spmm_rp(int relu, const void* arp, const int32_t* acol, const float* 
   while (ncb < NXCD && vec > ncb * 64) ncb *= 2;
   if (vec > ncb * 64) ncb = (vec + 63) / 64;
   const int64_t cv = (vec + ncb - 1) / ncb;
-  if (cv <= 2) return spmm_t<RP, 2, 4>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, ncb, s);
-  if (cv <= 4) return spmm_t<RP, 4, 4>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, ncb, s);
-  if (cv <= 8) return spmm_t<RP, 8, 4>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, ncb, s);
-  if (cv <= 16) return spmm_t<RP, 16, 4>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, ncb, s);
-  if (cv <= 32) return spmm_t<RP, 32, 4>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, ncb, s);
-  return spmm_t<RP, 64, 4>(relu, arp, acol, aval, m, W, ldw, F, Y, ldy, ncb, s);
+  if (cv <= 2) return spmm_t<RP, 2, 4>(relu, arp, acol, aval, m, nnz, W, ldw, F, Y, ldy, ncb, s);
+  if (cv <= 4) return spmm_t<RP, 4, 4>(relu, arp, acol, aval, m, nnz, W, ldw, F, Y, ldy, ncb, s);
+  if (cv <= 8) return spmm_t<RP, 8, 4>(relu, arp, acol, aval, m, nnz, W, ldw, F, Y, ldy, ncb, s);
+  if (cv <= 16) return spmm_t<RP, 16, 4>(relu, arp, acol, aval, m, nnz, W, ldw, F, Y, ldy, ncb, s);
+  if (cv <= 32) return spmm_t<RP, 32, 4>(relu, arp, acol, aval, m, nnz, W, ldw, F, Y, ldy, ncb, s);
+  return spmm_t<RP, 64, 4>(relu, arp, acol, aval, m, nnz, W, ldw, F, Y, ldy, ncb, s);
 }
 
 template <typename RP, int NT, bool VEC>
@@ -567,7 +587,7 @@ bool spmm_dense_fits(int64_t K, int64_t ldw) {
   return K >= 0 && K <= (int64_t(1) << 20) && ldw < (int64_t(1) << 23);
 }
 
-hipError_t spmm(const void* arp, int rpa64, const int32_t* acol, const float* aval, int64_t m, int64_t K,
+hipError_t spmm(const void* arp, int rpa64, const int32_t* acol, const float* aval, int64_t m, int64_t K, int64_t nnz,
                 const float* W, int64_t ldw, int64_t F, float* Y, int64_t ldy, int relu, int dense, hipStream_t s) {
   if (m <= 0 || F <= 0) return hipSuccess;
   if (dense) {
@@ -575,8 +595,8 @@ hipError_t spmm(const void* arp, int rpa64, const int32_t* acol, const float* av
     return rpa64 ? dense_rp<int64_t>(relu, arp, acol, aval, m, (int)K, W, ldw, (int)F, Y, ldy, s)
                  : dense_rp<int32_t>(relu, arp, acol, aval, m, (int)K, W, ldw, (int)F, Y, ldy, s);
   }
-  return rpa64 ? spmm_rp<int64_t>(relu, arp, acol, aval, m, W, ldw, (int)F, Y, ldy, s)
-               : spmm_rp<int32_t>(relu, arp, acol, aval, m, W, ldw, (int)F, Y, ldy, s);
+  return rpa64 ? spmm_rp<int64_t>(relu, arp, acol, aval, m, nnz, W, ldw, (int)F, Y, ldy, s)
+               : spmm_rp<int32_t>(relu, arp, acol, aval, m, nnz, W, ldw, (int)F, Y, ldy, s);
 }
 
 }  // namespace kern

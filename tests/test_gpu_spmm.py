@@ -147,6 +147,63 @@ def test_rows_lane_groups_and_column_blocks(torch_gpu, F):
     assert torch_gpu.isfinite(y).all()
 
 
+def rows_of(rng, lens, K):
+    """A CSR of these row lengths, one entry in each of as many equal parts
+    of the K columns, small integer values."""
+    lens = np.asarray(lens)
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    at = np.arange(rp[-1]) - np.repeat(rp[:-1], lens)
+    L = np.repeat(lens, lens)
+    lo, hi = at * K // L, (at + 1) * K // L
+    col = (lo + rng.integers(0, 1 << 30, len(at)) % (hi - lo)).astype(np.int32)
+    return CSR(len(lens), K, rp.astype(np.int32), col, rng.integers(-3, 4, len(at)).astype(np.float32))
+
+
+@pytest.mark.parametrize("F", [3, 64, 256, 516])
+def test_many_long_rows(torch_gpu, F):
+    """Long rows in every count: few (a group of rows each), many of like
+    length (the limit rises with the mean: a wavefront each), those with hubs
+    among them that stay split, and a ragged last group; integer values, so
+    the result is exact."""
+    rng = np.random.default_rng(40 + F)
+    K = 2048
+    mixed = rng.integers(250, 420, 3000)
+    mixed[rng.choice(3000, 40, replace=False)] = K
+    for lens in ([300] * 9, [K] * 65, [900] * 257, [257] * 700 + [3] * 400, mixed):
+        A = rows_of(rng, lens, K)
+        check(torch_gpu, A, rng.integers(-3, 4, (K, F)).astype(np.float32), relu=F == 64, rp64=F == 256, exact=True,
+              name="%d long rows F=%d" % (len(lens), F), algo="rows")
+
+
+@pytest.mark.parametrize("F", [64, 256])
+@pytest.mark.parametrize("m", [256, 4000, 20000])
+def test_many_long_rows_cost(torch_gpu, m, F):
+    """An entry costs about as much in rows just above the limit where rows
+    are split as in rows below it, however many there are (at most four times:
+    they were 15 to 40 times as dear while a workgroup looked through 512 rows
+    whatever their number)."""
+    import paper_2507_02006_amd as aires
+    rng = np.random.default_rng(m + F)
+    K = 4096
+    W = torch_gpu.from_numpy(rng.uniform(-1, 1, (K, F)).astype(np.float32)).cuda()
+    Y = torch_gpu.empty((m, F), device="cuda")
+    cost = {}
+    for L in (250, 300, 900):
+        A = dev_csr(torch_gpu, rows_of(rng, [L] * m, K))
+        best = float("inf")
+        for _ in range(5):
+            a, b = (torch_gpu.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(5):
+                aires.spmm(A, W, out=Y, algo="rows")
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        cost[L] = best / L
+    say("long rows m=%d F=%d: ns per call and entry of a row %s" % (m, F, {L: round(c * 2e5) for L, c in cost.items()}))
+    assert max(cost.values()) <= 4 * cost[250]
+
+
 @pytest.mark.parametrize("algo", ALGOS)
 def test_strides_offsets_and_rp64(torch_gpu, algo):
     """Row strides above F (padding untouched), a W base that is not
