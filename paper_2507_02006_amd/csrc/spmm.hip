@@ -39,9 +39,13 @@ constexpr int64_t kHeavyShare = 3072;
 // kHeavyGroups groups where each can have kHeavyGroup entries (256 rows of 900
 // entries, F = 64: 877 us in one group, 11 so). More would make the light rows
 // of a small launch wait (4000 rows of 200, F = 64: 12.3 us with 8 groups,
-// 12.5 with 256, 15.5 with 512).
+// 12.5 with 256, 15.5 with 512). Four blocks of columns and more make as many
+// workgroups of a group; there the large groups stay where rows are short on
+// average (symmetric R-MAT, 8000 rows of 13, F = 256: 18.8 us, 19.7 with small
+// groups; F = 128: 13.3 and 13.4, and 20000 rows of 13: 28.0 and 21.3).
 constexpr int64_t kHeavyGroups = 256;
 constexpr int64_t kHeavyGroup = 1024;
+constexpr int64_t kHeavyMean = 48;
 constexpr unsigned NXCD = 8;     // gfx950 hands workgroups round-robin to its 8 XCDs
 
 template <typename RP>
@@ -517,8 +521,9 @@ hipError_t spmm_t(int relu, const void* arp, const int32_t* acol, const float* a
   constexpr int HC = (L < 16 ? L : 16) * V;
   const int64_t hcb = (F + HC - 1) / HC;
   const int64_t heavy = std::max(kHeavy, std::min(2 * (nnz / m), nnz * ncb / kHeavyShare));
-  int64_t hx = std::max((m + SPMM_BLOCK - 1) / SPMM_BLOCK,
-                        std::min({m, nnz / kHeavyGroup, kHeavyGroups, 4 * kHeavyGroups / hcb}));
+  int64_t hx = (m + SPMM_BLOCK - 1) / SPMM_BLOCK;
+  if (hcb < 4 || nnz >= kHeavyMean * m)
+    hx = std::max(hx, std::min({m, nnz / kHeavyGroup, kHeavyGroups, 4 * kHeavyGroups / hcb}));
   hx = std::min(hx, hcb < 512 ? 4096 / hcb : 8);
   hx = (hx + NXCD - 1) / NXCD * NXCD;
   const int hrows = (int)std::min<int64_t>(SPMM_BLOCK, (m + hx - 1) / hx);
