@@ -46,6 +46,7 @@ constexpr int64_t kHeavyShare = 3072;
 constexpr int64_t kHeavyGroups = 256;
 constexpr int64_t kHeavyGroup = 1024;
 constexpr int64_t kHeavyMean = 48;
+constexpr int64_t kMaxCols = int64_t(1) << 20;  // columns of one launch
 constexpr unsigned NXCD = 8;     // gfx950 hands workgroups round-robin to its 8 XCDs
 
 template <typename RP>
@@ -600,8 +601,16 @@ hipError_t spmm(const void* arp, int rpa64, const int32_t* acol, const float* av
     return rpa64 ? dense_rp<int64_t>(relu, arp, acol, aval, m, (int)K, W, ldw, (int)F, Y, ldy, s)
                  : dense_rp<int32_t>(relu, arp, acol, aval, m, (int)K, W, ldw, (int)F, Y, ldy, s);
   }
-  return rpa64 ? spmm_rp<int64_t>(relu, arp, acol, aval, m, nnz, W, ldw, (int)F, Y, ldy, s)
-               : spmm_rp<int32_t>(relu, arp, acol, aval, m, nnz, W, ldw, (int)F, Y, ldy, s);
+  // a launch takes at most kMaxCols columns: its workgroups for heavy rows, eight
+  // or more to 64 columns, stay far below the 2^32 threads that a launch holds
+  // and column numbers past the end of a row below the largest int
+  hipError_t e = hipSuccess;
+  for (int64_t f0 = 0; f0 < F && e == hipSuccess; f0 += kMaxCols) {
+    const int f = (int)std::min(F - f0, kMaxCols);
+    e = rpa64 ? spmm_rp<int64_t>(relu, arp, acol, aval, m, nnz, W ? W + f0 : W, ldw, f, Y + f0, ldy, s)
+              : spmm_rp<int32_t>(relu, arp, acol, aval, m, nnz, W ? W + f0 : W, ldw, f, Y + f0, ldy, s);
+  }
+  return e;
 }
 
 }  // namespace kern

@@ -204,6 +204,32 @@ def test_many_long_rows_cost(torch_gpu, m, F):
     assert max(cost.values()) <= 4 * cost[250]
 
 
+@pytest.mark.parametrize("F", [(1 << 21) + 69, (1 << 26) + 5, (1 << 31) - 1])
+def test_widest_rows(torch_gpu, F):
+    """More columns than a launch takes, with split and light rows; so many
+    that one launch with workgroups for all their blocks was refused; and the
+    widest F there is: integer values, so the result is exact."""
+    import paper_2507_02006_amd as aires
+    torch = torch_gpu
+    lens = {21: [260, 3, 0, 259], 26: [2, 0, 1]}.get(F.bit_length() - 1, [1, 0])
+    K = max(lens)
+    rng = np.random.default_rng(F % 1000)
+    A = rows_of(rng, lens, K)
+    say("widest F=%d" % F)
+    W = torch.empty((K, F), device="cuda")
+    for k in range(K):
+        W[k] = (torch.arange(F, device="cuda", dtype=torch.int32) * (2 * k + 1) >> 3) % 7 - 3
+    Y = aires.spmm(dev_csr(torch, A), W, algo="rows")
+    for i in range(A.nrows):
+        y = torch.zeros(F, device="cuda")
+        for e in range(A.rp[i], A.rp[i + 1]):
+            y.add_(W[int(A.col[e])], alpha=float(A.val[e]))
+        assert torch.equal(Y[i], y), i
+        del y
+    del W, Y
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("algo", ALGOS)
 def test_strides_offsets_and_rp64(torch_gpu, algo):
     """Row strides above F (padding untouched), a W base that is not
