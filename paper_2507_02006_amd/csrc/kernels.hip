@@ -187,16 +187,19 @@ __global__ __launch_bounds__(1024) void k_analyze_long(const Operands op, int64_
 
 // ----------------------------------------------------------------- binning
 
-__device__ __forceinline__ int bin_of(const BinThresholds& th, int64_t p) {
+// The bin of a row of p products.  share: the bound of the bin whose bound
+// depends on the tile's products, from share_bound.  (It is compared on its own:
+// a copy of the thresholds with it filled in, at an index known at run time,
+// goes to scratch memory, a load per row and bin: 262144 rows, scatter 47 us
+// against 16.)
+__device__ __forceinline__ int bin_of(const BinThresholds& th, int64_t share, int64_t p) {
   int b = 0;
-  while (b < th.nb - 1 && p > th.max_p[b]) ++b;
+  while (b < th.nb - 1 && p > (b == th.share_bin ? share : th.max_p[b])) ++b;
   return b;
 }
 
-// the thresholds with the one that depends on the tile's products filled in
-__device__ __forceinline__ BinThresholds with_total(BinThresholds th, const unsigned long long* total) {
-  if (th.share_bin >= 0) th.max_p[th.share_bin] = max(th.max_p[th.share_bin], (int64_t)(*total / th.share));
-  return th;
+__device__ __forceinline__ int64_t share_bound(const BinThresholds& th, const unsigned long long* total) {
+  return th.share_bin < 0 ? 0 : max(th.max_p[th.share_bin], (int64_t)(*total / th.share));
 }
 
 // Bins are counted and filled per workgroup over a contiguous range of
@@ -207,17 +210,17 @@ __device__ __forceinline__ void block_rows(int64_t nrows, int64_t& r0, int64_t& 
   r1 = min(nrows, r0 + per);
 }
 
-__global__ __launch_bounds__(256) void k_bin_count(const int64_t* P, int64_t nrows, const BinThresholds th0,
+__global__ __launch_bounds__(256) void k_bin_count(const int64_t* P, int64_t nrows, const BinThresholds th,
                                                    const unsigned long long* total, int32_t* cnt,
                                                    const uint32_t* cbm, int words, int64_t* counts) {
-  const BinThresholds th = with_total(th0, total);
+  const int64_t share = share_bound(th, total);
   __shared__ int32_t h[MAX_BINS];
   if (threadIdx.x < MAX_BINS) h[threadIdx.x] = 0;
   __syncthreads();
   int64_t r0, r1;
   block_rows(nrows, r0, r1);
   for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) {
-    atomicAdd(&h[bin_of(th, P[i])], 1);
+    atomicAdd(&h[bin_of(th, share, P[i])], 1);
     if (cbm && counts[i] < 0) {  // a long row, whose bitmap is complete by now
       int c = 0;
       for (int w = 0; w < words; ++w) c += __popc(cbm[i * words + w]);
@@ -228,11 +231,11 @@ __global__ __launch_bounds__(256) void k_bin_count(const int64_t* P, int64_t nro
   if (threadIdx.x < th.nb && h[threadIdx.x]) atomicAdd(&cnt[threadIdx.x], h[threadIdx.x]);
 }
 
-__global__ __launch_bounds__(256) void k_bin_scatter(const int64_t* P, int64_t nrows, const BinThresholds th0,
+__global__ __launch_bounds__(256) void k_bin_scatter(const int64_t* P, int64_t nrows, const BinThresholds th,
                                                      const unsigned long long* total, const int32_t* cnt,
                                                      int32_t* cursor, int32_t* binoff,
                                                      int32_t* list) {
-  const BinThresholds th = with_total(th0, total);
+  const int64_t share = share_bound(th, total);
   __shared__ int32_t h[MAX_BINS], off[MAX_BINS + 1], base[MAX_BINS];
   if (threadIdx.x == 0) {
     int32_t s = 0;
@@ -245,7 +248,7 @@ __global__ __launch_bounds__(256) void k_bin_scatter(const int64_t* P, int64_t n
   __syncthreads();
   int64_t r0, r1;
   block_rows(nrows, r0, r1);
-  for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) atomicAdd(&h[bin_of(th, P[i])], 1);
+  for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) atomicAdd(&h[bin_of(th, share, P[i])], 1);
   __syncthreads();
   if (threadIdx.x < th.nb) {
     base[threadIdx.x] = h[threadIdx.x] ? atomicAdd(&cursor[threadIdx.x], h[threadIdx.x]) : 0;
@@ -253,7 +256,7 @@ __global__ __launch_bounds__(256) void k_bin_scatter(const int64_t* P, int64_t n
   }
   __syncthreads();
   for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) {
-    const int b = bin_of(th, P[i]);
+    const int b = bin_of(th, share, P[i]);
     list[off[b] + base[b] + atomicAdd(&h[b], 1)] = (int32_t)i;
   }
 }
@@ -1837,7 +1840,7 @@ constexpr int64_t SMALL_ROWS = (int64_t)SCAN_BLOCK * SMALL_PER;
 // at a time; a row's bin stays in a register between the count and the
 // scatter.
 template <bool BIN, bool SCAN>
-__global__ __launch_bounds__(SCAN_BLOCK) void k_small_rows(const int64_t* P, int n, const BinThresholds th0,
+__global__ __launch_bounds__(SCAN_BLOCK) void k_small_rows(const int64_t* P, int n, const BinThresholds th,
                                                           const unsigned long long* total, int32_t* binoff, int32_t* list, int64_t* x,
                                                           const int64_t* base, int64_t* end, const uint32_t* cbm,
                                                           int words) {
@@ -1853,14 +1856,14 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_small_rows(const int64_t* P, int
     for (int r = 0; r < SMALL_PER; ++r) v[r] = r < steps && i0 + r * WAVE < n ? x[i0 + r * WAVE] : 0;
   }
   if constexpr (BIN) {
-    const BinThresholds th = with_total(th0, total);
+    const int64_t share = share_bound(th, total);
     int64_t p[SMALL_PER];
 #pragma unroll
     for (int r = 0; r < SMALL_PER; ++r) p[r] = r < steps && i0 + r * WAVE < n ? P[i0 + r * WAVE] : -1;
     uint32_t bins = 0;  // 4 bits per row, 15: no row
 #pragma unroll
     for (int r = 0; r < SMALL_PER; ++r) {
-      if (r < steps) bins |= (uint32_t)(p[r] >= 0 ? bin_of(th, p[r]) : 15) << (4 * r);
+      if (r < steps) bins |= (uint32_t)(p[r] >= 0 ? bin_of(th, share, p[r]) : 15) << (4 * r);
     }
     for (int b = 0; b < MAX_BINS; ++b) {
       int mine = 0;
