@@ -353,10 +353,19 @@ namespace {
 // words) is at most 16 times the bytes of its columns on average: analysis and
 // symbolic phase of 60 K rows against 6001 columns, 30 entries a row (1 KB
 // against 120 bytes), 208 against 294 us; at 262144 rows against 512 columns,
-// 26 entries a row (64 against 104 bytes), 171 against 627 us.
-bool narrow_bitmaps_pay(const aires_csr& B) {
-  return B.ncols >= 1 && B.ncols <= kern::NARROW_MAX_COLS && B.nrows > 0 && B.nnz > 0 &&
-         kern::narrow_words(B.ncols) * B.nrows <= 16 * B.nnz;
+// 26 entries a row (64 against 104 bytes), 171 against 627 us.  Bitmaps and
+// slots are written for all of B, so A must read enough of its rows: from two
+// entries of A per row of B on, fewer where a row's bitmap and slot are small
+// (a million rows of B, a plan and product with / without them: 512 columns, 25
+// entries a row, one entry of A per row 567 / 502 us and two 724 / 734; 64
+// columns, 6 entries, a twentieth 321 / 292 and one 388 / 437).
+bool narrow_bitmaps_pay(const aires_csr& A, const aires_csr& B) {
+  if (B.ncols < 1 || B.ncols > kern::NARROW_MAX_COLS || B.nrows <= 0 || B.nnz <= 0) return false;
+  const int64_t words = kern::narrow_words(B.ncols);
+  kern::NarrowView v;
+  kern::narrow_slots(B.ncols, B.nrows, B.nnz, &v);
+  return words * B.nrows <= 16 * B.nnz &&
+         (double)A.nnz >= (double)B.nrows * (double)std::min<int64_t>(4 * words + v.slot, 320) / 160.0;
 }
 
 void bin_plan(aires_plan* p) {
@@ -441,7 +450,7 @@ void bin_plan(aires_plan* p) {
   // bins of a narrow product read through bitmaps (not where a hash limit or
   // a narrower dense row is asked for)
   kern::BinThresholds& tn = p->th_narrow;
-  if (N <= dense_max && o.hash_max_products == 0 && narrow_bitmaps_pay(p->B)) {
+  if (N <= dense_max && o.hash_max_products == 0 && narrow_bitmaps_pay(p->A, p->B)) {
     p->bitmaps = 1;
     // a wavefront's longest row at about a quarter of the mean work of the
     // chip's 8192 wavefront slots, so that it does not outlast the launch

@@ -155,3 +155,32 @@ def test_wide_dense_rows_split_in_parts(torch_gpu, N):
         rp, col, val, st = run(aires, torch_gpu, A, B, **kw)
         assert st["products"] == ref.products
         assert np.array_equal(rp, ref.rp) and np.array_equal(col, ref.col) and np.array_equal(val, ref.val)
+
+
+@pytest.mark.parametrize("N,mean,least", [(64, 6, 0.9), (512, 25, 2.0), (5000, 60, 2.0)])
+def test_bitmaps_of_b_only_for_enough_entries_of_a(torch_gpu, N, mean, least):
+    """Bitmaps (and slots) are written for every row of B, so a few rows of A
+    against a tall B must not ask for them: the call's device memory, counted
+    at the allocator, stays below what they take; from `least` entries of A per
+    row of B on they are there.  Integer values, so both are exact."""
+    import paper_2507_02006_amd as aires
+    from paper_2507_02006_amd import _binding as B_
+    rng = np.random.default_rng(N)
+    K = 60000
+    B = csr_of_lengths(rng, np.clip(rng.poisson(mean, K), 1, N), N, True)
+    dB = aires.to_device(B)
+    words = 4
+    while 32 * words < N:
+        words *= 2
+    for per_row, expect in ((0.01, False), (0.9 * least, False), (1.1 * least, True)):
+        A = csr_of_lengths(rng, np.full(int(K * per_row / 60), 60), K, True)
+        ref = oracle.spgemm(A, B)
+        log = B_.TorchAllocator(0)
+        with aires.tile_plan(aires.to_device(A), dB, 0, allocator=log, split_min_products=-1) as plan:
+            C = aires.spgemm(plan)
+            torch_gpu.cuda.synchronize()
+        extra = log.peak - 8 * ref.nnz  # without C's entries
+        print("[gpu-case] bitmaps N=%d nnz(A)/K=%.2f: %d bytes beside C" % (N, A.nnz / K, extra), flush=True)
+        assert (extra >= 4 * words * K) == expect
+        assert np.array_equal(C.rp.cpu().numpy(), ref.rp) and np.array_equal(C.col.cpu().numpy(), ref.col)
+        assert np.array_equal(C.val.cpu().numpy(), ref.val)
