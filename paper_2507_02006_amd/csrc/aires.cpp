@@ -361,6 +361,7 @@ namespace {
 // columns, 6 entries, a twentieth 321 / 292 and one 388 / 437).
 bool narrow_bitmaps_pay(const aires_csr& A, const aires_csr& B) {
   if (B.ncols < 1 || B.ncols > kern::NARROW_MAX_COLS || B.nrows <= 0 || B.nnz <= 0) return false;
+  if (B.nrows >= int64_t(1) << 30) return false;  // 64 rows to a workgroup of 256 threads, 2^32 threads to a launch
   const int64_t words = kern::narrow_words(B.ncols);
   kern::NarrowView v;
   kern::narrow_slots(B.ncols, B.nrows, B.nnz, &v);

@@ -184,3 +184,35 @@ def test_bitmaps_of_b_only_for_enough_entries_of_a(torch_gpu, N, mean, least):
         assert (extra >= 4 * words * K) == expect
         assert np.array_equal(C.rp.cpu().numpy(), ref.rp) and np.array_equal(C.col.cpu().numpy(), ref.col)
         assert np.array_equal(C.val.cpu().numpy(), ref.val)
+
+
+def test_b_of_two_to_the_thirty_rows(torch_gpu):
+    """As many rows of B as one launch that writes their bitmaps could not
+    hold: a quarter of them with one entry each, A with enough entries that
+    bitmaps would pay.  Counts, so exact."""
+    import paper_2507_02006_amd as aires
+    torch = torch_gpu
+    K, N, m, per = 1 << 30, 64, 4096, 27001
+    have = K // 4
+    brp = torch.arange(K + 1, dtype=torch.int32, device="cuda").clamp_(max=have)
+    bcol = torch.arange(have, dtype=torch.int32, device="cuda") % N
+    bval = torch.ones(have, device="cuda")
+    step = K // per
+    acol = (torch.arange(per, dtype=torch.int32, device="cuda") * step)[None, :] + (
+        torch.arange(m, dtype=torch.int32, device="cuda") * 7)[:, None]  # below step
+    assert (per - 1) * step + 7 * (m - 1) < K and 7 * (m - 1) < step
+    arp = torch.arange(m + 1, dtype=torch.int64, device="cuda") * per
+    A = (m, K, arp, acol.reshape(-1).contiguous(), torch.ones(m * per, device="cuda"))
+    print("[gpu-case] B of 2^30 rows", flush=True)
+    with aires.tile_plan(A, (K, N, brp, bcol, bval)) as plan:
+        C = aires.spgemm(plan)
+        torch.cuda.synchronize()
+    k = acol.long()
+    key = (torch.arange(m, device="cuda")[:, None] * N + k % N)[k < have]
+    count = torch.bincount(key, minlength=m * N).reshape(m, N)
+    lens = (count > 0).sum(1)
+    assert torch.equal(C.rp[1:] - C.rp[:-1], lens)
+    assert torch.equal(C.col.long(), count.nonzero()[:, 1])
+    assert torch.equal(C.val, count[count > 0].float())
+    del C, A, brp, bcol, bval, acol, k, key
+    torch.cuda.empty_cache()
