@@ -1938,10 +1938,11 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
   std::vector<int64_t> item_base((size_t)nt + 1, 0);
   if (p->wide)
     for (int64_t t = 0; t < nt; ++t) item_base[(size_t)t + 1] = item_base[(size_t)t] + host[(size_t)t].windows;
-  // C and the window list next to everything the call holds must fit the
-  // budget; the kept bitmaps are a cache and go first if they do not
-  const int64_t need = 8 * std::max<int64_t>(nnz, 1) + (int64_t)sizeof(kern::WinItem) *
-                                                          (p->wide ? std::max<int64_t>(item_base[(size_t)nt], 1) : 0);
+  // C (unless the caller holds it) and the window list next to everything the
+  // call holds must fit the budget; the kept bitmaps are a cache and go first if
+  // they do not
+  const int64_t need = (cc ? 0 : 8 * std::max<int64_t>(nnz, 1)) +
+                       (int64_t)sizeof(kern::WinItem) * (p->wide ? std::max<int64_t>(item_base[(size_t)nt], 1) : 0);
   if (bm_cache && !ws.fits(need)) {
     // the numeric phase then marks every window from the products
     ws.give_back(bm_cache);

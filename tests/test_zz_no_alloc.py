@@ -116,3 +116,41 @@ def test_noalloc_workspace_too_large(torch_gpu):
             aires.spgemm_noalloc(plan, rp, col, val)
         assert e.value.status == B_.E_CAPACITY and "scratch" in str(e.value)
         assert e.value.nnz == -1
+
+
+def _rows_of(rng, lens, ncols):
+    """Rows of these lengths, one entry in each of as many equal parts of the
+    columns, small integer values."""
+    lens = np.asarray(lens)
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    at = np.arange(rp[-1]) - np.repeat(rp[:-1], lens)
+    L = np.repeat(lens, lens)
+    lo, hi = at * ncols // L, (at + 1) * ncols // L
+    col = (lo + rng.integers(0, 1 << 30, len(at)) % (hi - lo)).astype(np.int32)
+    return CSR(len(lens), ncols, rp, col, rng.integers(-3, 4, len(at)).astype(np.float32))
+
+
+@pytest.mark.parametrize("m,N,mean", [(16000, 64, 6), (100000, 200, 20), (60000, 512, 20), (30000, 2000, 12)])
+def test_noalloc_keeps_the_bitmap_path(torch_gpu, m, N, mean):
+    """C lies in the caller's arrays, so its size says nothing about the fixed
+    workspace: an allocation-free call whose C is larger than what is left of
+    that keeps the bitmaps it has made.  Rows of few products and rows of 2000
+    take a bin each there, and are one bin of the general path, which runs all
+    of its bins where it takes over late: the launches of the numeric phase say
+    which one ran.  Integer values, so both calls are exact."""
+    import paper_2507_02006_amd as aires
+    rng = np.random.default_rng(N)
+    lens = np.full(m, 3)
+    lens[rng.choice(m, m // 200, replace=False)] = 2000 // mean
+    A, B = _rows_of(rng, lens, m), _rows_of(rng, np.full(m, mean), N)
+    say("allocation-free m=%d N=%d" % (m, N))
+    want, got = _pair(torch_gpu, A, B)
+    assert all(np.array_equal(x, y) for x, y in zip(want, got))
+    with aires.tile_plan(aires.to_device(A), aires.to_device(B), 0) as plan:
+        cap = len(want[1])
+        rp = torch_gpu.empty(m + 1, dtype=torch_gpu.int64, device="cuda")
+        col = torch_gpu.empty(cap, dtype=torch_gpu.int32, device="cuda")
+        val = torch_gpu.empty(cap, dtype=torch_gpu.float32, device="cuda")
+        assert aires.spgemm_noalloc(plan, rp, col, val) == cap
+        torch_gpu.cuda.synchronize()
+        assert aires.plan_stats(plan)["numeric_launches"] == 2
