@@ -355,18 +355,30 @@ namespace {
 // against 120 bytes), 208 against 294 us; at 262144 rows against 512 columns,
 // 26 entries a row (64 against 104 bytes), 171 against 627 us.  Bitmaps and
 // slots are written for all of B, so A must read enough of its rows: from two
-// entries of A per row of B on, fewer where a row's bitmap and slot are small
-// (a million rows of B, a plan and product with / without them: 512 columns, 25
-// entries a row, one entry of A per row 567 / 502 us and two 724 / 734; 64
-// columns, 6 entries, a twentieth 321 / 292 and one 388 / 437).
+// and a half entries of A per row of B on, fewer where a row's bitmap and slot
+// are small (a million rows of B, a plan and product with / without them: 512
+// columns, 25 entries a row, one entry of A per row 567 / 502 us and two 724 /
+// 734; 64 columns, 6 entries, a twentieth 321 / 292 and one 388 / 437; 20 K rows
+// of B, 3000 columns, 70 entries, two 352 / 337).
+// Few long rows of A are the general path's worst case (a workgroup per row, or
+// 32 with N <= kDenseWaveMaxN, for analysis and symbolic phase) and need a tenth
+// (8 rows, N = 200, 400 K rows of B, a fifth: 307 / 363 us); above that width,
+// where slots would take them a workgroup per row too, only without slots, and
+// as many products a row as last longer than the bitmaps at 1 us per 1000 (N =
+// 8000, 200 K rows of B, 24 M products: in one row 1140 us / 31 ms, in 64 of
+// 187 K at half as many 452 / 538).
 bool narrow_bitmaps_pay(const aires_csr& A, const aires_csr& B) {
-  if (B.ncols < 1 || B.ncols > kern::NARROW_MAX_COLS || B.nrows <= 0 || B.nnz <= 0) return false;
+  if (B.ncols < 1 || B.ncols > kern::NARROW_MAX_COLS || B.nrows <= 0 || B.nnz <= 0 || A.nrows <= 0) return false;
   if (B.nrows >= int64_t(1) << 30) return false;  // 64 rows to a workgroup of 256 threads, 2^32 threads to a launch
   const int64_t words = kern::narrow_words(B.ncols);
+  if (words * B.nrows > 16 * B.nnz) return false;
   kern::NarrowView v;
-  kern::narrow_slots(B.ncols, B.nrows, B.nnz, &v);
-  return words * B.nrows <= 16 * B.nnz &&
-         (double)A.nnz >= (double)B.nrows * (double)std::min<int64_t>(4 * words + v.slot, 320) / 160.0;
+  const bool slots = kern::narrow_slots(B.ncols, B.nrows, B.nnz, &v);
+  const double K = (double)B.nrows, bytes = (double)(4 * words + v.slot);
+  const double need = K * std::min(bytes, 400.0) / 160.0, mean = (double)A.nnz / (double)A.nrows;
+  if ((double)A.nnz >= need) return true;
+  if (B.ncols <= kDenseWaveMaxN) return mean >= 1024.0 && 10.0 * (double)A.nnz >= need;
+  return !slots && mean * ((double)B.nnz / K) * 1000.0 >= K * bytes;
 }
 
 void bin_plan(aires_plan* p) {

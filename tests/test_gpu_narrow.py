@@ -157,7 +157,7 @@ def test_wide_dense_rows_split_in_parts(torch_gpu, N):
         assert np.array_equal(rp, ref.rp) and np.array_equal(col, ref.col) and np.array_equal(val, ref.val)
 
 
-@pytest.mark.parametrize("N,mean,least", [(64, 6, 0.9), (512, 25, 2.0), (5000, 60, 2.0)])
+@pytest.mark.parametrize("N,mean,least", [(64, 6, 0.9), (512, 25, 2.0), (5000, 60, 2.5)])
 def test_bitmaps_of_b_only_for_enough_entries_of_a(torch_gpu, N, mean, least):
     """Bitmaps (and slots) are written for every row of B, so a few rows of A
     against a tall B must not ask for them: the call's device memory, counted
@@ -216,3 +216,31 @@ def test_b_of_two_to_the_thirty_rows(torch_gpu):
     assert torch.equal(C.val, count[count > 0].float())
     del C, A, brp, bcol, bval, acol, k, key
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("N,mean,m,length,expect", [(200, 20, 8, 1500, True), (200, 20, 8, 900, False), (64, 6, 2, 9000, True),
+                                                    (8000, 120, 1, 20000, True), (8000, 120, 30, 400, False),
+                                                    (4000, 100, 1, 20000, False)])
+def test_bitmaps_of_b_for_few_long_rows_of_a(torch_gpu, N, mean, m, length, expect):
+    """Few long rows of A take bitmaps (and slots) of B from far fewer entries
+    on: a row is one workgroup's work otherwise.  The device memory beside C
+    says which path ran; integer values, so both are exact."""
+    import paper_2507_02006_amd as aires
+    from paper_2507_02006_amd import _binding as B_
+    rng = np.random.default_rng(N + m)
+    K = 60000
+    B = csr_of_lengths(rng, np.clip(rng.poisson(mean, K), 1, N), N, True)
+    A = csr_of_lengths(rng, np.full(m, length), K, True)
+    words = 4
+    while 32 * words < N:
+        words *= 2
+    ref = oracle.spgemm(A, B)
+    log = B_.TorchAllocator(0)
+    with aires.tile_plan(aires.to_device(A), aires.to_device(B), 0, allocator=log, split_max_rows=1) as plan:
+        C = aires.spgemm(plan)
+        torch_gpu.cuda.synchronize()
+    extra = log.peak - 8 * ref.nnz
+    print("[gpu-case] long rows N=%d m=%d length=%d: %d bytes beside C" % (N, m, length, extra), flush=True)
+    assert (extra >= 4 * words * K) == expect
+    assert np.array_equal(C.rp.cpu().numpy(), ref.rp) and np.array_equal(C.col.cpu().numpy(), ref.col)
+    assert np.array_equal(C.val.cpu().numpy(), ref.val)
