@@ -28,6 +28,13 @@ namespace aires {
 namespace kern {
 namespace {
 
+// the value of lane i
+__device__ __forceinline__ int64_t lane_i64(int64_t v, int i) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, i);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), i);
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
 // -------------------------------------------------- B's bitmaps and slots
 
 // A slot holds a B row's first cap entries: cap values, then cap 16-bit
@@ -39,6 +46,8 @@ namespace {
 constexpr uint32_t GOES_ON = 0x8000u;
 
 __host__ __device__ constexpr int padded_cols(int64_t N) { return (int)((N + 63) / 64 * 64); }
+
+constexpr int64_t PREPARE_LONG = 256;  // entries of a row of B
 
 // One pass over B writes both.  16 lanes per row; bitmaps and slots of the
 // workgroup's rows are put together in LDS and go out as whole lines.
@@ -56,12 +65,11 @@ __global__ __launch_bounds__(256) void k_narrow_prepare(const void* brp, const i
   const int nr = (int)(K - r0 < rows ? K - r0 : rows);
   for (int i = threadIdx.x; i < rows * words; i += 256) bm[i] = 0u;
   __syncthreads();
-  for (int r = sg; r < nr; r += 16) {
-    const int64_t s = ld_rp<RB>(brp, r0 + r), e = ld_rp<RB>(brp, r0 + r + 1);
-    const int64_t len = e - s;
+  // entries from q on, `step` apart, of row r: [s, s + len) of B's arrays
+  auto put_row = [&](int r, int64_t s, int64_t len, int64_t q, int step) {
     float* sv = reinterpret_cast<float*>(sl + (size_t)r * slot);
     uint16_t* sc = reinterpret_cast<uint16_t*>(sv + cap);
-    for (int64_t q = sub; q < len || q < cap; q += 16) {
+    for (; q < len || q < cap; q += step) {
       uint32_t c = no_col;
       float v = 0.f;
       if (q < len) {
@@ -74,6 +82,22 @@ __global__ __launch_bounds__(256) void k_narrow_prepare(const void* brp, const i
         sv[q] = v;
         sc[q] = (uint16_t)c;
       }
+    }
+  };
+  for (int rb = 0; rb < nr; rb += 16) {
+    const int r = rb + sg;
+    int64_t s = 0, len = -1;
+    if (r < nr) {
+      s = ld_rp<RB>(brp, r0 + r);
+      len = ld_rp<RB>(brp, r0 + r + 1) - s;
+    }
+    const bool is_long = len > PREPARE_LONG;
+    if (r < nr && !is_long) put_row(r, s, len, sub, 16);
+    // long rows by the whole wavefront (30 K rows, 60 of them of 8000 entries: 147
+    // us with 16 lanes to each)
+    for (uint64_t todo = __ballot(is_long && sub == 0); todo; todo &= todo - 1u) {
+      const int l = __builtin_ctzll(todo);
+      put_row(__builtin_amdgcn_readlane(r, l), lane_i64(s, l), lane_i64(len, l), lane_id(), WAVE);
     }
   }
   __syncthreads();
@@ -243,12 +267,6 @@ __global__ __launch_bounds__(256) void k_narrow_long(const Operands op, const Na
 }
 
 // ----------------------------------------------------------------- numeric
-
-__device__ __forceinline__ int64_t lane_i64(int64_t v, int i) {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, i);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), i);
-  return (int64_t)(((uint64_t)hi << 32) | lo);
-}
 
 __device__ __forceinline__ int lanes_below(uint64_t bits) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(bits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bits, 0u));

@@ -244,3 +244,36 @@ def test_bitmaps_of_b_for_few_long_rows_of_a(torch_gpu, N, mean, m, length, expe
     assert (extra >= 4 * words * K) == expect
     assert np.array_equal(C.rp.cpu().numpy(), ref.rp) and np.array_equal(C.col.cpu().numpy(), ref.col)
     assert np.array_equal(C.val.cpu().numpy(), ref.val)
+
+
+@pytest.mark.parametrize("N", [1024, 8192])
+def test_long_rows_of_b_do_not_hold_up_the_bitmaps(torch_gpu, N):
+    """Rows of B with an entry in every column, which A does not touch: writing
+    their bitmaps (and slots) costs a call at most 75 us (8192 entries read 16
+    at a time took 120)."""
+    import paper_2507_02006_amd as aires
+    torch = torch_gpu
+    rng = np.random.default_rng(N)
+    K = 20000
+    lens = rng.poisson(60, K)
+    full = np.arange(7, K, 500)
+    A = csr_of_lengths(rng, np.full(8000, 16), K - len(full), True)
+    A = CSR(A.nrows, K, A.rp, np.setdiff1d(np.arange(K), full)[A.col].astype(np.int32), A.val)
+    best = {}
+    for name in ("short", "long"):
+        if name == "long":
+            lens[full] = N
+        B = csr_of_lengths(np.random.default_rng(1), lens, N, True)
+        dA, dB = aires.to_device(A), aires.to_device(B)
+        best[name] = float("inf")
+        for _ in range(15):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            torch.cuda.synchronize()
+            a.record()
+            with aires.tile_plan(dA, dB) as plan:
+                aires.spgemm(plan)
+            b.record()
+            b.synchronize()
+            best[name] = min(best[name], a.elapsed_time(b) * 1e3)
+    print("[gpu-case] full rows of B, N=%d: %s us" % (N, best), flush=True)
+    assert best["long"] <= best["short"] + 75.0
