@@ -298,11 +298,15 @@ constexpr int WPL = WINDOW / WAVE;
 // g], so that the G sums of a column are one vector, with one column more for
 // what is not used; then a window of A's entries.  S lanes take one B row:
 // entry sl and, where slots hold more than S (TWO: S < cap <= 2 S), entry S +
-// sl; rows above cap go on in B's arrays.
-template <typename RB, int S, bool TWO>
+// sl; rows above cap go on in B's arrays, with O loads of each array in flight
+// where DEEP (k_narrow_block; rows of 600 entries in slots of 106, 47 M
+// products: 312 us with one at a time).  In k_narrow_rows, whose rows are short
+// and registers few, that cost 5 % (N = 4000, 240 M products: 1154 -> 1203 us).
+template <typename RB, int S, bool TWO, bool DEEP = false>
 struct DenseRows {
   static constexpr int G = WAVE / S;
   static constexpr int U = 4;  // steps (of G entries) in flight together
+  static constexpr int O = 4;
   static_assert(G * U <= WINDOW_PAD, "a step reads at most the padding past the window");
   unsigned char* acc;
   Entry* win;
@@ -400,6 +404,25 @@ struct DenseRows {
           x = en.a;
           q = ld_rp<RB>(op.brp, k) + cap + sl;
           end = ld_rp<RB>(op.brp, k + 1);
+        }
+        if constexpr (DEEP) {
+          for (; __any(q < end); q += O * S) {
+            uint32_t col[O];
+            float b[O];
+#pragma unroll
+            for (int i = 0; i < O; ++i) {
+              const int64_t at = q + i * S < end ? q + i * S : 0;
+              col[i] = (uint32_t)op.bcol[at] * (4u * G);
+              b[i] = op.bval[at];
+            }
+            wave_sync();
+#pragma unroll
+            for (int i = 0; i < O; ++i) {
+              if (i && !__any(q + i * S < end)) break;
+              put(q + i * S < end ? col[i] : no_col, x, b[i]);
+            }
+          }
+          continue;
         }
         for (; __any(q < end); q += S) {
           uint32_t col = no_col;
@@ -562,7 +585,7 @@ template <typename RA, typename RB, int S, bool TWO, bool SPLIT, int NWV>
 __global__ __launch_bounds__(NWV* WAVE, NWV) void k_narrow_block(const Operands op, const NarrowView nv, const BinView bv,
                                                                const SplitWs sw, const Outputs out) {
   extern __shared__ __align__(16) unsigned char smem[];
-  using DR = DenseRows<RB, S, TWO>;
+  using DR = DenseRows<RB, S, TWO, true>;
   const int N = (int)op.N, Np = padded_cols(N);
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
   const int lane = lane_id();
