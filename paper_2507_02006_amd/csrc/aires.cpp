@@ -2106,7 +2106,7 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
   } slot[2];
   int32_t* bidx = nullptr;
   kern::TileInfo* info = nullptr;
-  ST_TRY(ws.get_n(nt + 1, &info));  // info[t + 1]: tile t; info[0].end = 0, the start of C.row_ptr
+  ST_TRY(ws.get_n(2, &info));  // tiles take them in turn; info[1].end = 0 starts C.row_ptr
   if (p->wide) ST_TRY(ws.get_n(index_words(p), &bidx));
   kern::SplitWs split{};
   ST_TRY(alloc_split_ws(p, ws, max_rows, split));
@@ -2158,7 +2158,7 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
                         hipHostMallocDefault));
   hb.v.push_back(info_host);
   kern::ClearList clears;  // with the first tile's
-  clears.add(&info->end, sizeof info->end);
+  clears.add(&info[1].end, sizeof info->end);
 
   std::vector<hipEvent_t> evs;
   struct EvGuard {
@@ -2339,9 +2339,11 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
     }
     kern::Operands op = tile_operands(p, tile_rp, T.nnz0, S.acol, S.aval, brp, bcol, bval, bidx);
     tm.tile = (int)t;
-    S.w.info = info + t + 1;
+    // (tile t - 2 is done with its info when this one's kernels run, and its copy
+    // to the host was waited for)
+    S.w.info = info + t % 2;
     S.w.host = info_host + t;
-    ST_TRY(tile_symbolic(p, op, k, T.nnz1 - T.nnz0, S.w, S.crp, &info[t].end, clears, sc, tm));
+    ST_TRY(tile_symbolic(p, op, k, T.nnz1 - T.nnz0, S.w, S.crp, &info[(t + 1) % 2].end, clears, sc, tm));
     clears = kern::ClearList{};
     HIP_TRY(hipMemcpyAsync(info_host + t, S.w.info, sizeof(kern::TileInfo), hipMemcpyDeviceToHost, sc));
     HIP_TRY(hipEventRecord(ev_cnt[(size_t)t], sc));

@@ -256,3 +256,26 @@ def test_streamed_budget_and_tiles(torch_gpu, c_on_host):
             assert t["d2h_begin_ms"] == -1.0
     for t in range(info.ntiles - 1):
         assert ts[t + 1]["h2d_begin_ms"] < ts[t]["compute_end_ms"], t
+
+
+def test_streamed_tiles_beyond_the_planners_slack(torch_gpu):
+    """66 000 tiles under exactly the planned peak: what the library keeps per
+    tile on the device does not grow with their number."""
+    import paper_2507_02006_amd as aires
+    from workloads import CSR
+    m = 66000
+    rng = np.random.default_rng(12)
+    A = CSR(m, 64, np.arange(m + 1, dtype=np.int64), rng.integers(0, 64, m).astype(np.int32),
+            rng.integers(1, 4, m).astype(np.float32))
+    B = CSR(64, 40, np.arange(65, dtype=np.int64), (np.arange(64) * 7 % 40).astype(np.int32),
+            np.arange(1, 65, dtype=np.float32))
+    hA, hB = aires.to_pinned(A), aires.to_pinned(B)
+    with aires.tile_plan(hA, hB, 1 << 30, c_on_host=True, max_tile_rows=1) as plan:
+        peak, nt = aires.plan_info(plan).peak_bytes, aires.plan_info(plan).ntiles
+    assert nt == m
+    say("streamed: %d tiles under %d bytes" % (nt, peak))
+    with aires.tile_plan(hA, hB, peak, c_on_host=True, max_tile_rows=1) as plan:
+        C = aires.spgemm(plan)
+        assert np.array_equal(C.rp, np.arange(m + 1))
+        assert np.array_equal(C.col, B.col[A.col]) and np.array_equal(C.val, A.val * B.val[A.col])
+        del C
