@@ -107,7 +107,8 @@ typedef struct aires_csr_out {
  * Optional device-memory allocator.  alloc returns device memory usable on
  * `stream` (a hipStream_t) or NULL on failure; free releases it
  * stream-ordered on `stream`.  A NULL return makes the call fail with
- * AIRES_E_OOM after releasing what it had allocated.
+ * AIRES_E_OOM after releasing what it had allocated, unless the request was
+ * for workspace that the call can do without (see aires_spgemm, Memory).
  */
 typedef struct aires_allocator {
     void *(*alloc)(void *ctx, size_t bytes, void *stream);
@@ -396,8 +397,14 @@ aires_status aires_plan_tile(const aires_plan *plan, int64_t t, aires_tile *tile
  * Memory (the constraint M of Sec. III-A): every block the call takes from
  * the allocator, C included, counts against the plan's budget together
  * with the caller's device-resident inputs; an allocation that would pass
- * it fails the call with AIRES_E_BUDGET (the kept symbolic bitmaps, a
- * cache, are dropped first).  Every block is requested and released on
+ * it fails the call with AIRES_E_BUDGET.  What the budget leaves beyond
+ * peak_bytes may be taken for workspace that makes the call faster: the kept
+ * symbolic bitmaps of wide rows, the presence bitmaps and slots of B's rows
+ * (N <= 8192) with the bitmaps of C's, the dense slots of hub rows of
+ * products of 2049 to dense_max_cols columns.  Such workspace goes before C
+ * is refused, and the call does without it where the allocator refuses it
+ * (of bitmaps and slots of B, a block of more than 4 MiB; a smaller refusal
+ * is AIRES_E_OOM).  Every block is requested and released on
  * `stream` (the allocator's stream argument), so an allocator that pools
  * per stream never hands a block still in use by this call to other work.
  * Errors: AIRES_E_INVALID_ARG, AIRES_E_STATE (C not zeroed / plan busy),

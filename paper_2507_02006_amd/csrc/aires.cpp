@@ -1515,12 +1515,23 @@ int64_t optional_room(const aires_plan* p, const DevPool& ws) {
   return ws.arena ? (ws.left() - (int64_t(64) << 10)) / 2 : p->budget - p->info.peak_bytes - ws.optional;
 }
 
+// Workspace that the call can do without: *out stays NULL where the allocator
+// refuses it.  Where it refuses a block no larger than the slack that the plan
+// counts on, there is no memory for the rest of the call either, and the call
+// ends (AIRES_E_OOM).
+aires_status get_optional(DevPool& ws, int64_t bytes, void** out) {
+  *out = nullptr;
+  const aires_status st = ws.get((size_t)bytes, out);
+  return st == AIRES_E_OOM && bytes > kFixedWorkspace ? AIRES_OK : st;
+}
+
 // The bitmaps of B's rows (K) and of C's rows (rows in all), the slots of B's
 // rows and the part list of a tile of up to nnz entries are optional
 // workspace: taken where the budget left free by the plan (or half of what
 // is left of a fixed arena) holds them, so that no call needs more than it
 // was planned with.  One block holds them all.  copies: how many of the C
-// bitmaps and part lists are needed (two slots of a streamed A).
+// bitmaps and part lists are needed (two slots of a streamed A).  Asked for
+// after everything the plan counted.
 aires_status alloc_narrow(aires_plan* p, DevPool& ws, int64_t rows, int64_t nnz, int copies, kern::NarrowView* nv) {
   for (int i = 0; i < copies; ++i) nv[i] = kern::NarrowView{};
   // (C's arrays under Eq. 5 are an estimate that may have to grow)
@@ -1541,7 +1552,8 @@ aires_status alloc_narrow(aires_plan* p, DevPool& ws, int64_t rows, int64_t nnz,
   if (!fits() && slots) slots = false;
   if (!fits()) return AIRES_OK;
   void* block = nullptr;
-  ST_TRY(ws.get((size_t)need, &block));
+  ST_TRY(get_optional(ws, need, &block));
+  if (!block) return AIRES_OK;
   ws.optional += need;
   char* at = static_cast<char*>(block);
   auto carve = [&](int64_t bytes) {
@@ -1579,26 +1591,9 @@ aires_status alloc_tile_ws(aires_plan* p, DevPool& ws, int64_t n, bool with_list
   return AIRES_OK;
 }
 
-aires_status alloc_split_ws(aires_plan* p, DevPool& ws, int64_t rows, kern::SplitWs& sw) {
+aires_status alloc_split_ws(aires_plan* p, DevPool& ws, kern::SplitWs& sw) {
   sw = kern::SplitWs{};
   const int64_t N = p->B.ncols;
-  if (p->split_wide) {
-    // as many slots as rows, the default and what the plan leaves free allow;
-    // rows without one take a workgroup each
-    const int64_t nwd = (N + 31) / 32;
-    const int64_t room = std::min(optional_room(p, ws), ws.left()) - 512;
-    int64_t cap = std::min(rows, p->opts.split_max_rows > 0 ? p->opts.split_max_rows : kSplitRowsWide);
-    cap = std::min(cap, room / (4 * (nwd + N)));
-    // (Eq. 5's estimate of C may have to grow into the free budget)
-    if (cap < 1 || (p->info.a_streamed && p->opts.c_bound == AIRES_CBOUND_PAPER_EQ5)) return AIRES_OK;
-    uint32_t* block = nullptr;
-    ST_TRY(ws.get_n(cap * (nwd + N), &block));
-    ws.optional += 4 * cap * (nwd + N);
-    sw.bm = block;
-    sw.acc = reinterpret_cast<float*>(block + cap * nwd);
-    sw.cap = cap;
-    return AIRES_OK;
-  }
   if (!p->split) return AIRES_OK;
   int64_t cap = p->split_cap;
   if (ws.arena) {
@@ -1612,6 +1607,55 @@ aires_status alloc_split_ws(aires_plan* p, DevPool& ws, int64_t rows, kern::Spli
   ST_TRY(ws.get_n(cap * N, &sw.acc));
   sw.cap = cap;
   return AIRES_OK;
+}
+
+// The bins of a call: by what the slots make of a row, or the general ones
+// (up to kDenseWaveMaxN columns both have dense kinds only, and the first suit
+// the general kernels too: 1900 rows squared, numeric phase 69 against 113 us).
+const kern::BinThresholds& call_bins(const aires_plan* p, const kern::NarrowView& nv) {
+  return nv.words && (nv.slots || p->B.ncols <= kDenseWaveMaxN) ? p->th_narrow : p->th;
+}
+
+// The numeric phase reads B's slots: they pay while the B rows that the products
+// touch mostly fit them.
+bool reads_slots(const TileWs& w, int64_t nnz) {
+  return w.narrow.words && w.narrow.slots && (int64_t)w.host->products <= nnz * w.narrow.cap;
+}
+
+// The tile's rows were binned for the slots, which it does not read: they are
+// binned again for the general path.
+bool bins_again(const aires_plan* p, const TileWs& w, bool slots) {
+  return w.rebin || (&call_bins(p, w.narrow) == &p->th_narrow && !slots && p->B.ncols > kDenseWaveMaxN);
+}
+
+// Wide split rows of a tile of nnz entries whose symbolic phase is done (where its
+// rows are binned again, as many as its products allow).
+int64_t split_wide_rows(const aires_plan* p, const TileWs& w, int64_t nnz) {
+  if (!p->split_wide) return 0;
+  const kern::BinThresholds& th = p->th;
+  const int bin = th.nb - 1;  // KIND_DENSE_SPLIT
+  if (bins_again(p, w, reads_slots(w, nnz))) return (int64_t)w.host->products / (th.max_p[bin - 1] + 1);
+  return &call_bins(p, w.narrow) == &th ? w.host->binoff[bin + 1] - w.host->binoff[bin] : 0;
+}
+
+// Slots for them, in the memory that is left beside C, at most as many as the
+// default allows; rows without one take a workgroup each.  Slots already there
+// are kept, or given back for more.
+void fit_split_wide(const aires_plan* p, DevPool& ws, int64_t rows, kern::SplitWs& sw) {
+  // (Eq. 5's estimate of C may have to grow into the free budget)
+  if (!p->split_wide || (p->info.a_streamed && p->opts.c_bound == AIRES_CBOUND_PAPER_EQ5)) return;
+  const int64_t N = p->B.ncols, nwd = (N + 31) / 32, per = 4 * (nwd + N);
+  const int64_t most = p->opts.split_max_rows > 0 ? p->opts.split_max_rows : kSplitRowsWide;
+  const int64_t left = std::min(ws.left(), INT64_MAX / 2) + per * sw.cap - 512;
+  const int64_t cap = std::min({rows, most, left / per});
+  if (cap <= sw.cap) return;
+  if (sw.bm) ws.give_back(sw.bm);
+  sw = kern::SplitWs{};
+  uint32_t* block = nullptr;
+  if (ws.get_n(cap * (nwd + N), &block) != AIRES_OK) return;
+  sw.bm = block;
+  sw.acc = reinterpret_cast<float*>(block + cap * nwd);
+  sw.cap = cap;
 }
 
 // The slots of a tile's split rows (wide ones: with the products per row).
@@ -1644,13 +1688,6 @@ kern::WindowParams window_params(const aires_plan* p, const TileWs& w) {
   wp.slab_bin = p->slab_bin;
   wp.nslab = 1;  // set at the numeric launch from its grid
   return wp;
-}
-
-// The bins of a call: by what the slots make of a row, or the general ones
-// (up to kDenseWaveMaxN columns both have dense kinds only, and the first suit
-// the general kernels too: 1900 rows squared, numeric phase 69 against 113 us).
-const kern::BinThresholds& call_bins(const aires_plan* p, const kern::NarrowView& nv) {
-  return nv.words && (nv.slots || p->B.ncols <= kDenseWaveMaxN) ? p->th_narrow : p->th;
 }
 
 // analyze + bin + symbolic + scan of one tile; counts land in crp[1..n] and
@@ -1724,11 +1761,10 @@ aires_status tile_numeric(aires_plan* p, const kern::Operands& op, int64_t n, in
   out.crp = crp;
   out.ccol = ccol - c_base;
   out.cval = cval - c_base;
-  // slots pay while the B rows that the products touch mostly fit them
-  const bool slots = w.narrow.words && w.narrow.slots && (int64_t)w.host->products <= nnz * w.narrow.cap;
+  const bool slots = reads_slots(w, nnz);
   const int e0 = tm.record();
   const kern::BinThresholds* th = &call_bins(p, w.narrow);
-  const bool rebin = w.rebin || (th == &p->th_narrow && !slots && p->B.ncols > kDenseWaveMaxN);
+  const bool rebin = bins_again(p, w, slots);
   if (rebin) {
     // the rows were binned for the slots: bin them for the general path (how
     // many a bin holds stays on the device; n bounds it)
@@ -1878,8 +1914,10 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
   bool rebin = false;
   int64_t max_nnz = 0;
   for (const auto& t : p->tiles) max_nnz = std::max(max_nnz, t.nnz1 - t.nnz0);
+  if (!ws.arena) ST_TRY(alloc_split_ws(p, ws, shared.split));
   ST_TRY(alloc_narrow(p, ws, m, max_nnz, 1, &narrow));
-  ST_TRY(alloc_split_ws(p, ws, max_rows, shared.split));
+  const int64_t narrow_bytes = ws.optional;
+  if (ws.arena) ST_TRY(alloc_split_ws(p, ws, shared.split));  // takes what is left
   auto tile_ws = [&](int64_t t) {
     const aires_tile& T = p->tiles[(size_t)t];
     TileWs w = shared;
@@ -1961,17 +1999,21 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
     bm_cache = nullptr;
     bm_cap = 0;
   }
-  if (narrow.words && !ws.fits(need)) {
-    // the bitmaps of a narrow product go before C is refused too: the general
-    // numeric kernels need only the row bins
+  // the bitmaps of a narrow product go before C is refused too: the general
+  // numeric kernels need only the row bins
+  auto drop_narrow = [&] {
     ws.give_back(const_cast<uint32_t*>(narrow.bbm));  // the first part of their block
     rebin = &call_bins(p, narrow) != &p->th;
     narrow.words = 0;
-  }
-  if (p->split_wide && shared.split.cap > 0 && !ws.fits(need)) {
-    ws.give_back(shared.split.bm);
-    shared.split = kern::SplitWs{};
-  }
+  };
+  if (narrow.words && !ws.fits(need)) drop_narrow();
+  // an array of C; refused by the allocator, once more without them
+  auto get_c = [&](auto** x) {
+    const aires_status st = ws.get_n(nnz, x);
+    if (st != AIRES_E_OOM || !narrow.words || narrow_bytes <= kFixedWorkspace) return st;
+    drop_narrow();
+    return ws.get_n(nnz, x);
+  };
   int32_t* ccol = nullptr;
   float* cval = nullptr;
   if (cc) {
@@ -1986,10 +2028,19 @@ aires_status spgemm_device_in(aires_plan* p, hipStream_t s, DevPool& ws, aires_c
                   "C needs %lld bytes (and its window list %lld); the budget of %lld bytes leaves %lld",
                   (long long)(8 * nnz), (long long)(need - 8 * nnz), (long long)p->budget,
                   (long long)(ws.cap - ws.used));
-    ST_TRY(ws.get_n(nnz, &ccol));
-    ST_TRY(ws.get_n(nnz, &cval));
+    ST_TRY(get_c(&ccol));
+    ST_TRY(get_c(&cval));
   }
   if (p->wide) ST_TRY(ws.get_n(item_base[(size_t)nt], &items));
+  int64_t wide_rows = 0;
+  for (int64_t t = 0; t < nt; ++t) {
+    const aires_tile& T = p->tiles[(size_t)t];
+    TileWs w = tile_ws(t);
+    w.host = &host[(size_t)t];
+    w.rebin = rebin;
+    wide_rows = std::max(wide_rows, split_wide_rows(p, w, T.nnz1 - T.nnz0));
+  }
+  fit_split_wide(p, ws, wide_rows, shared.split);
 
   // Sweep 2: numeric phase of every tile.
   for (int64_t t = 0; t < nt; ++t) {
@@ -2109,9 +2160,7 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
   ST_TRY(ws.get_n(2, &info));  // tiles take them in turn; info[1].end = 0 starts C.row_ptr
   if (p->wide) ST_TRY(ws.get_n(index_words(p), &bidx));
   kern::SplitWs split{};
-  ST_TRY(alloc_split_ws(p, ws, max_rows, split));
-  kern::NarrowView narrow[2];
-  ST_TRY(alloc_narrow(p, ws, max_rows, max_q, 2, narrow));
+  ST_TRY(alloc_split_ws(p, ws, split));
   for (int s = 0; s < 2; ++s) {
     Slot& S = slot[s];
     S = Slot{};
@@ -2119,8 +2168,6 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
     ST_TRY(ws.get_n(max_q, &S.acol));
     ST_TRY(ws.get_n(max_q, &S.aval));
     ST_TRY(alloc_tile_ws(p, ws, max_rows, true, S.w));
-    S.w.split = split;
-    S.w.narrow = narrow[s];
     ST_TRY(ws.get_n(max_rows + 1, &S.crp));
     if (c_on_host) {
       ST_TRY(ws.get_n(max_cb, &S.ccol));
@@ -2320,6 +2367,13 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
     HIP_TRY(kern::build_window_index(brp, B.rp_type == AIRES_IDX_I64, bcol, bval, K, p->G, p->nG, bidx,
                                      index_bmax(p, bidx), sc));
   }
+  // optional workspace, after all that the plan counted
+  kern::NarrowView narrow[2];
+  ST_TRY(alloc_narrow(p, ws, max_rows, max_q, 2, narrow));
+  for (int i = 0; i < 2; ++i) {
+    slot[i].w.split = split;
+    slot[i].w.narrow = narrow[i];
+  }
   if (narrow[0].words && nt > 0) {
     HIP_TRY(hipStreamWaitEvent(sc, ev_in[0], 0));
     HIP_TRY(kern::narrow_prepare(brp, B.rp_type == AIRES_IDX_I64, bcol, bval, K, N, narrow[0], sc));
@@ -2412,6 +2466,8 @@ aires_status stream_impl(aires_plan* p, hipStream_t sh, hipStream_t sc, hipStrea
         S.icap = grow;
       }
     }
+    fit_split_wide(p, ws, split_wide_rows(p, S.w, T.nnz1 - T.nnz0), split);
+    S.w.split = split;
     if (c_on_host) {
       ST_TRY(tile_numeric(p, op, k, T.nnz1 - T.nnz0, S.w, S.crp, S.ccol, S.cval, base, sc, tm));
     } else {

@@ -279,3 +279,99 @@ def test_streamed_tiles_beyond_the_planners_slack(torch_gpu):
         assert np.array_equal(C.rp, np.arange(m + 1))
         assert np.array_equal(C.col, B.col[A.col]) and np.array_equal(C.val, A.val * B.val[A.col])
         del C
+
+
+class LimitedAllocator:
+    """torch-backed allocator that refuses single blocks above `block` bytes
+    and requests that would take it past `total` bytes in all."""
+
+    def __init__(self, block=1 << 62, total=1 << 62):
+        from paper_2507_02006_amd import _binding as B_
+        self.inner = B_.TorchAllocator(0)
+        self.block, self.total = block, total
+        self.refused = []
+        self._alloc = B_.ALLOC_FN(self._alloc_cb)
+        self.struct = B_.Allocator(self._alloc, self.inner._free, None)
+        self.take = self.inner.take
+
+    def _alloc_cb(self, ctx, nbytes, stream):
+        if nbytes > self.block or self.inner.cur + nbytes > self.total:
+            self.refused.append(nbytes)
+            return None
+        return self.inner._alloc_cb(ctx, nbytes, stream)
+
+
+def rows_of(rng, lens, K):
+    """Rows of these lengths, one entry in each of as many equal parts of the
+    K columns, small integer values."""
+    lens = np.asarray(lens)
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    at = np.arange(rp[-1]) - np.repeat(rp[:-1], lens)
+    L = np.repeat(lens, lens)
+    lo, hi = at * K // L, (at + 1) * K // L
+    col = (lo + rng.integers(0, 1 << 30, len(at)) % (hi - lo)).astype(np.int32)
+    return workloads.CSR(len(lens), K, rp, col, rng.integers(-3, 4, len(at)).astype(np.float32))
+
+
+@pytest.mark.parametrize("streamed", [False, True])
+@pytest.mark.parametrize("what", ["bitmaps", "c", "split"])
+def test_optional_workspace_refused(torch_gpu, what, streamed):
+    """Workspace beyond the plan's peak is not needed: where the allocator
+    refuses B's bitmaps and slots (or the slots of hub rows), or C beside them,
+    the call gives the result without them.  Integer values, so exact."""
+    import paper_2507_02006_amd as aires
+    from paper_2507_02006_amd import _binding as B_
+    rng = np.random.default_rng(17)
+    if what == "split":
+        A, B, kw = rows_of(rng, [100] * 1000, 3000), rows_of(rng, [50] * 3000, 12000), dict(split_min_products=2000)
+    else:
+        A, B, kw = rows_of(rng, [8] * 16000, 40000), rows_of(rng, [60] * 40000, 1500), dict(split_min_products=-1)
+    ref = oracle.spgemm(A, B)
+    put = aires.to_pinned if streamed else aires.to_device
+    dA, dB = put(A), put(B)
+    kw["c_on_host"] = streamed
+
+    def run(alloc):
+        with aires.tile_plan(dA, dB, 0, allocator=alloc, **kw) as plan:
+            C = aires.spgemm(plan)
+            torch_gpu.cuda.synchronize()
+            rp, col, val = (x if streamed else x.cpu().numpy() for x in (C.rp, C.col, C.val))
+            assert np.array_equal(rp, ref.rp) and np.array_equal(col, ref.col) and np.array_equal(val, ref.val)
+            del C, rp, col, val
+
+    probe = LimitedAllocator()
+    run(probe)
+    peak = probe.inner.peak
+    if what == "bitmaps":
+        limited = LimitedAllocator(block=32 << 20)  # 40000 x (256 + 512) bytes and more
+    elif what == "split":
+        limited = LimitedAllocator(block=20 << 20)  # 1000 x 49.5 KB
+    else:
+        limited = LimitedAllocator(total=peak - 1)
+    run(limited)
+    say("optional %s streamed=%d: peak %d, refused %s" % (what, streamed, peak, limited.refused))
+    assert len(limited.refused) >= 1 and limited.inner.cur == 0
+    assert max(limited.refused) > 4 << 20
+
+
+def test_split_slots_only_for_rows_that_need_them(torch_gpu):
+    """A product of 12000 columns without hub rows takes no dense slots (1024 of
+    them are 50 MB); with three it takes three."""
+    import paper_2507_02006_amd as aires
+    from paper_2507_02006_amd import _binding as B_
+    rng = np.random.default_rng(18)
+    B = rows_of(rng, [50] * 3000, 12000)
+    dB = aires.to_device(B)
+    extra = []
+    for lens in ([20] * 2000, [20] * 1997 + [2500] * 3):
+        A = rows_of(rng, lens, 3000)
+        ref = oracle.spgemm(A, B)
+        log = B_.TorchAllocator(0)
+        with aires.tile_plan(aires.to_device(A), dB, 0, allocator=log) as plan:
+            C = aires.spgemm(plan)
+            torch_gpu.cuda.synchronize()
+        extra.append(log.peak - 8 * ref.nnz)
+        assert np.array_equal(C.col.cpu().numpy(), ref.col) and np.array_equal(C.val.cpu().numpy(), ref.val)
+        del C
+    say("split slots: %s bytes beside C" % extra)
+    assert extra[0] < 1 << 20 and 3 * 4 * 12000 <= extra[1] - extra[0] < 4 * 4 * (12000 + 375)
