@@ -99,26 +99,91 @@ def test_long_rows_in_parts(torch_gpu):
         assert np.array_equal(rp, ref.rp) and np.array_equal(col, ref.col) and np.array_equal(val, ref.val)
 
 
-@pytest.mark.parametrize("N,mean", [(64, 6), (500, 22), (2048, 100), (5000, 50)])
-def test_against_the_general_kernels(torch_gpu, N, mean):
-    """The same plan with no room for bitmaps and slots: the same structure, and
-    values within the bound of two fp32 sums of n terms, gamma_n sum |a b|
-    each; infinite and NaN entries reach the same entries of C."""
+class LoggingAllocator:
+    """torch-backed allocator that keeps the sizes it handed out and got back."""
+
+    def __init__(self):
+        from paper_2507_02006_amd import _binding as B_
+        self.inner = B_.TorchAllocator(0)
+        self.events, self.size = [], {}
+        self._alloc, self._free = B_.ALLOC_FN(self._alloc_cb), B_.FREE_FN(self._free_cb)
+        self.struct = B_.Allocator(self._alloc, self._free, None)
+        self.take = self.inner.take
+
+    def _alloc_cb(self, ctx, nbytes, stream):
+        at = self.inner._alloc_cb(ctx, nbytes, stream)
+        self.size[at] = nbytes
+        self.events.append(nbytes)
+        return at
+
+    def _free_cb(self, ctx, ptr, stream):
+        self.events.append(-self.size.pop(ptr, 0))
+        self.inner._free_cb(ctx, ptr, stream)
+
+
+@pytest.mark.parametrize("N,mean,K,m", [(64, 6, 9000, 10400), (500, 22, 6000, 1700), (2048, 100, 2000, 400),
+                                        (5000, 50, 2000, 500)])
+def test_against_the_general_kernels(torch_gpu, N, mean, K, m):
+    """The same product by the general kernels (a hash limit asks for them), with
+    no room for bitmaps and slots, with room for the bitmaps alone, and with
+    room for both but not for C beside them, so that they are given back: the
+    same structure, and values within the bound of two fp32 sums of n terms,
+    gamma_n sum |a b| each; infinite and NaN entries reach the same entries of
+    C.  The sizes asked of the allocator say which of these it was."""
     import paper_2507_02006_amd as aires
     rng = np.random.default_rng(N)
-    A, B = operands(rng, N, mean, ints=False)
+    lb = np.clip(rng.poisson(mean, K), 0, N)
+    lb[rng.choice(K, K // 20, replace=False)] = 0
+    lb[rng.choice(K, 5, replace=False)] = N
+    B = csr_of_lengths(rng, lb, N, False)
+    la = np.concatenate([np.array([0, 1, 1, 2, 7, 8, 9, 31, 32, 33, 63, 64, 65, 127, 128, 129, 257, 400, K, 1, 0, 1]),
+                         rng.integers(0, 60, m), np.ones(40, int)])
+    A = csr_of_lengths(rng, la, K, False)
     A.val[rng.choice(len(A.val), 3, replace=False)] = [np.inf, -np.inf, np.nan]
-    nnz = int(oracle.spgemm(A, B).rp[-1])
-    probe_rp, probe_col, probe_val, _ = run(aires, torch_gpu, A, B)
     dA, dB = aires.to_device(A), aires.to_device(B)
-    with aires.tile_plan(dA, dB, split_min_products=-1) as plan:
-        peak = aires.plan_info(plan).peak_bytes
-    # what the plan needs, with no room left for the bitmaps; then with room for
-    # them but not for C beside them, so that they are given back
-    room = 8 * nnz + 4096
-    for extra in (room, room + 4 * 256 * (A.nrows + B.nrows)):
-        rp, col, val, _ = run(aires, torch_gpu, A, B, (False, False), hbm_budget=peak + extra, split_min_products=-1)
-        compare(A, B, rp, col, val, probe_rp, probe_col, probe_val)
+    inputs = A.nbytes() + B.nbytes()
+
+    def go(budget, **kw):
+        log = LoggingAllocator()
+        with aires.tile_plan(dA, dB, budget, allocator=log, split_min_products=-1, **kw) as plan:
+            planned = aires.plan_info(plan).peak_bytes
+            C = aires.spgemm(plan)
+            torch_gpu.cuda.synchronize()
+        return C.rp.cpu().numpy(), C.col.cpu().numpy(), C.val.cpu().numpy(), log, planned
+
+    *ref, log, planned = go(0)
+    *gen, glog, _ = go(0, hash_max_products=4096)
+    both = log.inner.peak - glog.inner.peak
+    bits = 256 * (-(-4 * narrow_words(N) * K // 256) + -(-4 * narrow_words(N) * A.nrows // 256))
+    assert both >= bits and both in log.events and both not in glog.events
+    compare(A, B, *gen, *ref)
+    least = inputs + glog.inner.peak  # holds C and the general path's workspace
+    print("[gpu-case] general path N=%d: C %d, bitmaps and slots %d bytes" % (N, 8 * len(ref[1]), both), flush=True)
+    # no room for the bitmaps
+    assert least - planned < bits
+    *got, log, _ = go(max(planned + 1, least))
+    assert log.inner.peak == glog.inner.peak
+    compare(A, B, *got, *ref)
+    # room for them, but not for C beside them
+    budget = max(planned + both, least)
+    assert budget < least + both
+    *got, log, _ = go(budget)
+    assert both in log.events and log.events.index(-both) < log.events.index(4 * len(ref[1]))
+    compare(A, B, *got, *ref)
+    if both > bits + 4096:  # slots too: room for the bitmaps alone, and C beside them
+        budget = planned + both - 1
+        assert least + bits + 65536 <= budget
+        *got, log, _ = go(budget)
+        taken = log.inner.peak - glog.inner.peak
+        assert bits <= taken < bits + 65536
+        compare(A, B, *got, *ref)
+
+
+def narrow_words(N):
+    words = 4
+    while 32 * words < N:
+        words *= 2
+    return words
 
 
 def compare(A, B, rp, col, val, probe_rp, probe_col, probe_val):
@@ -132,7 +197,7 @@ def compare(A, B, rp, col, val, probe_rp, probe_col, probe_val):
     mag = oracle.spgemm(Aabs, CSR(B.nrows, B.ncols, B.rp, B.col, np.abs(B.val)))
     n = np.repeat(np.diff(A.rp), np.diff(rp))
     bound = 2 * (n + 2) * 2.0 ** -24 * mag.val
-    assert np.all(np.abs(val.astype(np.float64) - probe_val)[fin] <= bound[fin] + 1e-30)
+    assert np.all(np.abs(val[fin].astype(np.float64) - probe_val[fin]) <= bound[fin] + 1e-30)
 
 
 @pytest.mark.parametrize("N", [2049, 5000, 12001, 16384])
@@ -169,9 +234,7 @@ def test_bitmaps_of_b_only_for_enough_entries_of_a(torch_gpu, N, mean, least):
     K = 60000
     B = csr_of_lengths(rng, np.clip(rng.poisson(mean, K), 1, N), N, True)
     dB = aires.to_device(B)
-    words = 4
-    while 32 * words < N:
-        words *= 2
+    words = narrow_words(N)
     for per_row, expect in ((0.01, False), (0.9 * least, False), (1.1 * least, True)):
         A = csr_of_lengths(rng, np.full(int(K * per_row / 60), 60), K, True)
         ref = oracle.spgemm(A, B)
@@ -231,9 +294,7 @@ def test_bitmaps_of_b_for_few_long_rows_of_a(torch_gpu, N, mean, m, length, expe
     K = 60000
     B = csr_of_lengths(rng, np.clip(rng.poisson(mean, K), 1, N), N, True)
     A = csr_of_lengths(rng, np.full(m, length), K, True)
-    words = 4
-    while 32 * words < N:
-        words *= 2
+    words = narrow_words(N)
     ref = oracle.spgemm(A, B)
     log = B_.TorchAllocator(0)
     with aires.tile_plan(aires.to_device(A), aires.to_device(B), 0, allocator=log, split_max_rows=1) as plan:
