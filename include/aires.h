@@ -471,7 +471,11 @@ typedef struct aires_stats {
     /* milliseconds from HIP events (opts->timing), summed over tiles.
        h2d_ms / d2h_ms: busy time of the copy streams (events around each
        tile's copies, after its waits).  total_ms: the whole call on the
-       compute stream, output allocation included.                        */
+       compute stream, output allocation included.  Where B's rows are read
+       as presence bitmaps (N <= 8192), the symbolic pass counts the
+       products too: analyze_ms is 0 and its time stands under dense-wave
+       in kind_ms[0]; up to 8192 rows one kernel bins and scans, counted
+       in bin_ms.                                                          */
     double analyze_ms, bin_ms, symbolic_ms, scan_ms, numeric_ms;
     double h2d_ms, d2h_ms, total_ms;
     int64_t numeric_launches;   /* numeric-phase kernel launches           */

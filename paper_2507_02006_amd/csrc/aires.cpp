@@ -1707,12 +1707,21 @@ aires_status tile_symbolic(aires_plan* p, const kern::Operands& op, int64_t n, i
     HIP_TRY(kern::clear_words(cl, s));
     HIP_TRY(kern::narrow_symbolic(op, n, nnz, w.narrow, w.P, crp + 1, &info->products, s));
     const int e1 = tm.record();
-    HIP_TRY(kern::bin_and_scan(w.P, n, call_bins(p, w.narrow), &info->products, w.cntcur, info->binoff, w.list, &w.narrow, crp + 1, base, &info->end,
-                               w.scan_ws, s));
-    const int e2 = tm.record();
+    int e2 = e1;
+    if (kern::few_rows(n)) {  // one launch for both
+      HIP_TRY(kern::bin_and_scan(w.P, n, call_bins(p, w.narrow), &info->products, info->binoff, w.list, w.narrow,
+                                 crp + 1, base, &info->end, s));
+    } else {
+      HIP_TRY(kern::bin_rows(w.P, n, call_bins(p, w.narrow), &info->products, w.cntcur, info->binoff, w.list,
+                             &w.narrow, crp + 1, s));
+      e2 = tm.record();
+      HIP_TRY(kern::scan_inplace(crp + 1, n, base, &info->end, w.scan_ws, s));
+    }
+    const int e3 = tm.record();
     tm.mark(kern::KIND_DENSE_WAVE, 0, e0, e1);
     tm.mark(PH_SYMBOLIC, 0, e0, e1);
-    tm.mark(PH_SCAN, 0, e1, e2);
+    tm.mark(PH_BIN, 0, e1, e2 > e1 ? e2 : e3);
+    if (e2 > e1) tm.mark(PH_SCAN, 0, e2, e3);
     return AIRES_OK;
   }
   cl.add(crp + 1, sizeof(int64_t) * std::max<int64_t>(n, 0));

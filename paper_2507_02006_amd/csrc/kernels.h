@@ -179,11 +179,12 @@ hipError_t build_window_index(const void* brp, int rpb64, const int32_t* bcol, c
 // sum_{j<=i} x[j]; *end (may be nullptr) receives the last one.
 size_t scan_workspace_bytes(int64_t n);
 hipError_t scan_inplace(int64_t* x, int64_t n, const int64_t* base, int64_t* end, void* ws, hipStream_t s);
-// bin_rows, then scan_inplace of the counts x (a launch for both where the rows are few)
+// bin_rows and scan_inplace of the counts x of a tile with bitmaps, in one launch
+// where the rows are few (few_rows)
+bool few_rows(int64_t n);
 hipError_t bin_and_scan(const int64_t* P, int64_t n, const BinThresholds& th, const unsigned long long* total,
-                        int32_t* cnt_cursor, int32_t* binoff,
-                        int32_t* list, const NarrowView* nv, int64_t* x, const int64_t* base, int64_t* end, void* ws,
-                        hipStream_t s);
+                        int32_t* binoff, int32_t* list, const NarrowView& nv, int64_t* x, const int64_t* base,
+                        int64_t* end, hipStream_t s);
 // Clears n arrays of 32-bit words in one launch.
 struct ClearList {
   static constexpr int MAX = 8;

@@ -2128,7 +2128,7 @@ hipError_t analyze(const Operands& op, int64_t nrows, int64_t* P, unsigned long 
 
 hipError_t bin_rows(const int64_t* P, int64_t nrows, const BinThresholds& th, const unsigned long long* total,
                     int32_t* cnt_cursor, int32_t* binoff, int32_t* list, const NarrowView* nv, int64_t* counts, hipStream_t s) {
-  if (nrows > 0 && nrows <= SMALL_ROWS && !nv) {
+  if (few_rows(nrows) && !nv) {
     hipLaunchKernelGGL((k_small_rows<true, false>), dim3(1), dim3(SCAN_BLOCK), 0, s, P, (int)nrows, th, total, binoff, list,
                        nullptr, nullptr, nullptr, nullptr, 0);
     return hipGetLastError();
@@ -2194,22 +2194,20 @@ hipError_t clear_words(const ClearList& cl, hipStream_t s) {
   return hipGetLastError();
 }
 
+bool few_rows(int64_t n) { return n > 0 && n <= SMALL_ROWS; }
+
 hipError_t bin_and_scan(const int64_t* P, int64_t n, const BinThresholds& th, const unsigned long long* total,
-                        int32_t* cnt_cursor, int32_t* binoff,
-                        int32_t* list, const NarrowView* nv, int64_t* x, const int64_t* base, int64_t* end, void* ws,
-                        hipStream_t s) {
-  if (n > SMALL_ROWS || n <= 0) {
-    hipError_t e = bin_rows(P, n, th, total, cnt_cursor, binoff, list, nv, x, s);
-    return e != hipSuccess ? e : scan_inplace(x, n, base, end, ws, s);
-  }
+                        int32_t* binoff, int32_t* list, const NarrowView& nv, int64_t* x, const int64_t* base,
+                        int64_t* end, hipStream_t s) {
+  if (!few_rows(n)) return hipErrorInvalidValue;
   hipLaunchKernelGGL((k_small_rows<true, true>), dim3(1), dim3(SCAN_BLOCK), 0, s, P, (int)n, th, total, binoff, list,
-                     x, base, end, nv ? nv->cbm : nullptr, nv ? nv->words : 0);
+                     x, base, end, nv.cbm, nv.words);
   return hipGetLastError();
 }
 
 hipError_t scan_inplace(int64_t* x, int64_t n, const int64_t* base, int64_t* end, void* ws, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  if (n <= SMALL_ROWS) {
+  if (few_rows(n)) {
     hipLaunchKernelGGL((k_small_rows<false, true>), dim3(1), dim3(SCAN_BLOCK), 0, s, nullptr, (int)n, BinThresholds{},
                        nullptr, nullptr, nullptr, x, base, end, nullptr, 0);
     return hipGetLastError();

@@ -338,3 +338,20 @@ def test_long_rows_of_b_do_not_hold_up_the_bitmaps(torch_gpu, N):
             best[name] = min(best[name], a.elapsed_time(b) * 1e3)
     print("[gpu-case] full rows of B, N=%d: %s us" % (N, best), flush=True)
     assert best["long"] <= best["short"] + 75.0
+
+
+@pytest.mark.parametrize("m", [5000, 20000])
+def test_phase_times_of_the_bitmap_path(torch_gpu, m):
+    """The times of a call with bitmaps: products are counted in the symbolic
+    pass (no analysis), binning is a phase of its own, and the scan too where
+    the rows are not few."""
+    import paper_2507_02006_amd as aires
+    rng = np.random.default_rng(m)
+    A, B = csr_of_lengths(rng, [9] * m, 4000, True), csr_of_lengths(rng, [12] * 4000, 128, True)
+    with aires.tile_plan(aires.to_device(A), aires.to_device(B), timing=True) as plan:
+        aires.spgemm(plan)
+        torch_gpu.cuda.synchronize()
+        st, tile = aires.plan_stats(plan), aires.plan_tile_stats(plan, 0)
+    for x in (st, tile):
+        assert x["analyze_ms"] == 0.0 and x["symbolic_ms"] > 0.0 and x["numeric_ms"] > 0.0
+        assert x["bin_ms"] > 0.0 and (x["scan_ms"] > 0.0) == (m > 8192)
