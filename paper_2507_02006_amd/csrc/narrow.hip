@@ -469,25 +469,21 @@ struct DenseRows {
 };
 
 constexpr int MAX_ROWS_PER_TURN = 16;   // consecutive rows a wavefront takes at a time
-constexpr int NARROW_WAVES = 1;         // wavefronts of a k_narrow_rows workgroup
 
 // Rows with 0 < P_i <= max_p, `turn` consecutive ones to a wavefront.
 // Rows of a single entry (isolated vertices: their C row is a_ik times B_k)
 // come first, a lane group each.  The entries of the others are one run of A,
 // read a window at a time whatever rows they belong to.
 template <typename RA, typename RB, int S, bool TWO>
-__global__ __launch_bounds__(NARROW_WAVES* WAVE, 8) void k_narrow_rows(const Operands op, const NarrowView nv,
-                                                                    const int64_t* P, int64_t nrows, int64_t max_p,
-                                                                    int turn, const Outputs out) {
+__global__ __launch_bounds__(WAVE, 8) void k_narrow_rows(const Operands op, const NarrowView nv, const int64_t* P,
+                                                         int64_t nrows, int64_t max_p, int turn, const Outputs out) {
   extern __shared__ __align__(16) unsigned char smem[];
   using DR = DenseRows<RB, S, TWO>;
   const int N = (int)op.N, Np = padded_cols(N);
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
   const int lane = lane_id(), sl = lane % S;
-  DR D(NARROW_WAVES > 1 ? smem + wv * DR::bytes(Np) : smem, nv, Np);
+  DR D(smem, nv, Np);
   D.clear(Np);
-  const int64_t nw = (int64_t)gridDim.x * NARROW_WAVES;
-  for (int64_t r0 = ((int64_t)blockIdx.x * NARROW_WAVES + wv) * turn; r0 < nrows; r0 += nw * turn) {
+  for (int64_t r0 = (int64_t)blockIdx.x * turn; r0 < nrows; r0 += (int64_t)gridDim.x * turn) {
     const int nr = (int)(nrows - r0 < turn ? nrows - r0 : turn);
     int64_t rp = 0, crp = 0, prods = 0;
     if (lane <= nr) rp = ld_rp<RA>(op.arp, r0 + lane) - op.a_base;
@@ -729,15 +725,15 @@ hipError_t rows_t(const Operands& op, const NarrowView& nv, const int64_t* P, in
                   const Outputs& out, hipStream_t s) {
   auto kern = k_narrow_rows<RA, RB, S, TWO>;
   const int Np = padded_cols(op.N);
-  const size_t lds = NARROW_WAVES * DenseRows<RB, S, TWO>::bytes(Np);
+  const size_t lds = DenseRows<RB, S, TWO>::bytes(Np);
   hipError_t e = allow_lds(kern, lds);
   if (e != hipSuccess) return e;
   // few rows: fewer to a turn, so that every wavefront slot of the chip has some
-  const int64_t slots = NARROW_WAVES * resident_blocks(kern, NARROW_WAVES * WAVE, lds);
+  const int64_t slots = resident_blocks(kern, WAVE, lds);
   const int turn = (int)std::max<int64_t>(1, std::min<int64_t>(MAX_ROWS_PER_TURN, nrows / slots));
-  const int64_t need = (nrows + NARROW_WAVES * turn - 1) / (NARROW_WAVES * turn);
+  const int64_t need = (nrows + turn - 1) / turn;
   const int64_t grid = std::min<int64_t>(need, 1 << 20);
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NARROW_WAVES * WAVE), lds, s, op, nv, P, nrows, max_p, turn,
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(WAVE), lds, s, op, nv, P, nrows, max_p, turn,
                      out);
   return hipGetLastError();
 }
@@ -813,7 +809,7 @@ int32_t narrow_words(int64_t N) {
 // rows of a feature matrix are longer), in whole 64-byte blocks, for at most
 // twice the lanes that take a row.  The lanes: the power of two from 1.25 mu
 // on, at least 8, and enough that a wavefront's dense rows (64 / lanes of N
-// floats) stay within 8 KB.
+// floats) stay within 8 KB (above 2048 columns: 64 lanes, up to 16 KB).
 bool narrow_slots(int64_t N, int64_t K, int64_t nnz, NarrowView* nv) {
   nv->lanes = nv->cap = nv->slot = 0;
   if (K <= 0 || nnz <= 0 || N > NARROW_SLOT_COLS) return false;
