@@ -527,7 +527,8 @@ hipError_t spmm_t(int relu, const void* arp, const int32_t* acol, const float* a
     hx = std::max(hx, std::min({m, nnz / kHeavyGroup, kHeavyGroups, 4 * kHeavyGroups / hcb}));
   hx = std::min(hx, hcb < 512 ? 4096 / hcb : 8);
   hx = (hx + NXCD - 1) / NXCD * NXCD;
-  const int hrows = (int)std::min<int64_t>(SPMM_BLOCK, (m + hx - 1) / hx);
+  int hrows = (int)std::min<int64_t>(SPMM_BLOCK, (m + hx - 1) / hx);
+  if (hrows > SPMM_BLOCK / 2) hrows = SPMM_BLOCK;
   const int64_t hblocks = hx * hcb;
   const int64_t nside = NXCD / (ncb < NXCD ? ncb : NXCD);
   int64_t g = (m + nside * NWV - 1) / (nside * NWV);
