@@ -375,3 +375,27 @@ def test_split_slots_only_for_rows_that_need_them(torch_gpu):
         del C
     say("split slots: %s bytes beside C" % extra)
     assert extra[0] < 1 << 20 and 3 * 4 * 12000 <= extra[1] - extra[0] < 4 * 4 * (12000 + 375)
+
+
+def test_split_slots_grow_over_streamed_tiles(torch_gpu):
+    """Streamed tiles with more and more hub rows, up to the cap and beyond it,
+    then none: the slots are given back for more between tiles that still run.
+    Integer values, so exact."""
+    import paper_2507_02006_amd as aires
+    rng = np.random.default_rng(19)
+    lens = []
+    for hubs in (0, 2, 1, 5, 9, 0, 14, 3):
+        lens += [1500] * hubs + [7] * (16 - hubs)
+    A, B = rows_of(rng, lens, 3000), rows_of(rng, [50] * 3000, 12000)
+    ref = oracle.spgemm(A, B)
+    hA, hB = aires.to_pinned(A), aires.to_pinned(B)
+    for c_on_host in (True, False):
+        for cap in (0, 8):
+            with aires.tile_plan(hA, hB, 0, c_on_host=c_on_host, max_tile_rows=16, split_min_products=20000,
+                                 split_max_rows=cap) as plan:
+                assert aires.plan_info(plan).ntiles == 8
+                C = aires.spgemm(plan)
+                torch_gpu.cuda.synchronize()
+                rp, col, val = (x if c_on_host else x.cpu().numpy() for x in (C.rp, C.col, C.val))
+                assert np.array_equal(rp, ref.rp) and np.array_equal(col, ref.col) and np.array_equal(val, ref.val)
+                del C, rp, col, val

@@ -76,8 +76,9 @@ def check(torch, A, W, relu=False, rp64=False, ldw_pad=0, ldy_pad=0, w_offset=0,
 @pytest.mark.parametrize("algo", ALGOS)
 @pytest.mark.parametrize("F", [1, 7, 64, 65, 100, 128, 129, 200, 256, 512, 700])
 def test_widths(torch_gpu, F, algo):
-    """Rows: one wavefront pass covers 64*V columns (V = 1, 2, 4, 8); 700
-    takes two passes; F not a multiple of the vector takes the scalar tail.
+    """Rows: lane groups of 16-byte loads up to 64 lanes wide, one column a
+    lane below four columns; 512 and 700 take several column blocks; where F
+    is not a multiple of four the last lane's vector is moved back.
     Dense tiles: 64- or 128-column tiles, ragged in m (300), K (90) and F."""
     rng = np.random.default_rng(F)
     A = workloads.random_csr(rng, 300, 90, 0.05)
@@ -106,8 +107,8 @@ def _csr_parts(D):
 
 @pytest.mark.parametrize("algo", ALGOS)
 def test_heavy_rows_split_over_a_workgroup(torch_gpu, algo):
-    """Rows above 512 entries take the workgroup kernel (four wavefronts
-    and an LDS reduction); mixed with light and empty rows.  For dense
+    """Rows above the limit for one wavefront take the eight wavefronts of a
+    workgroup (and an LDS reduction); mixed with light and empty rows.  For dense
     tiles, rows with more than 32 entries in a 64-column chunk take several
     load rounds."""
     rng = np.random.default_rng(7)
@@ -233,7 +234,7 @@ def test_widest_rows(torch_gpu, F):
 @pytest.mark.parametrize("algo", ALGOS)
 def test_strides_offsets_and_rp64(torch_gpu, algo):
     """Row strides above F (padding untouched), a W base that is not
-    vector-aligned (scalar loads), and 64-bit row pointers."""
+    vector-aligned, and 64-bit row pointers."""
     rng = np.random.default_rng(8)
     A = workloads.random_csr(rng, 200, 70, 0.1)
     W = rng.uniform(-1, 1, (70, 256)).astype(np.float32)
